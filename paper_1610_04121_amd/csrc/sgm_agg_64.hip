@@ -1,0 +1,10 @@
+// The aggregation launch of pairs padded to 64 disparity levels.
+#include "sgm_agg_impl.h"
+
+namespace sgm {
+
+hipError_t launch_agg_64(const AggArgs& a, const AggVariant& v, hipStream_t stream) {
+    return launch_agg_dp<64>(a, v, stream);
+}
+
+}  // namespace sgm

@@ -22,6 +22,7 @@
 
 #include "../../include/sgm.h"
 #include "sgm_batch.h"
+#include "sgm_batch_agg.h"
 #include "sgm_device.h"
 #include "sgm_plan.h"
 
@@ -30,37 +31,6 @@ namespace sgm {
 namespace {
 
 using namespace dev;
-
-// One pair as the batched kernels see it.
-struct BatchItem {
-    const uint8_t* left;
-    const uint8_t* right;
-    uint16_t* out;
-    uint64_t* census_l;
-    uint64_t* census_r;
-    uint8_t* cost;
-    uint8_t* cost_r;  // right-base costs (lr_full), else nullptr
-    void* lbuf;       // L_r planes; with lr_full the right-base planes follow
-    uint16_t* dl;
-    uint16_t* dr;
-    int W, H, D, Dp, P, cmax, l16, median, lrcheck, thr, csct, gh, gv, subpixel, lr_full, adaptive;
-    int census_blk0, cost_blk0, wta_blk0, post_blk0;  // first block in each launch
-};
-
-// One aggregation work item: S = 64 / G slices of one direction of one pair;
-// rb = 1 for a direction of the right-base SGM (full left-right check);
-// item = -1 marks an empty place of a quad.
-struct WorkItem {
-    int item, plane, rx, ry, first, steps, rb;
-};
-
-// Work items go out four at a time, one per wavefront of a workgroup (a
-// quad).  Opposite directions over the same pixels share a quad (A, A, B,
-// B): the axis-aligned ones over the same two slice groups, the diagonals
-// over the groups that cover (most of) the same pixels.  Both walks over a
-// pixel's costs then run on one CU and its L2, and the second read can hit
-// there, as in the single-pair aggregation launch.
-constexpr int kQuad = 4;
 
 // Index of the pair whose block range [blk0, next blk0) holds block b.
 template <int BatchItem::*FIRST>
@@ -120,91 +90,6 @@ __global__ __launch_bounds__(kCostThreads) void cost_batch_kernel(const BatchIte
     } else {
         local -= nx * it.H;
         cost_batch_block<true>(it, local % nx, local / nx, cost_smem);
-    }
-}
-
-// NT: non-temporal L_r stores (the batch's planes exceed the memory-side
-// cache); ADAPT: adaptive P2 (the block's penalty table is in s.p2lut).
-template <typename LT, int Dp, bool NT, bool ADAPT>
-__device__ __attribute__((always_inline)) inline void aggregate_item(const SliceArgs& s, int kind, int g, int first,
-                                                                     int lane) {
-    if (kind == kHoriz) {
-        if (g == 32)
-            aggregate_wave<32, Dp / 32, LT, kHoriz, false, ADAPT, NT>(s, first, lane);
-        else
-            aggregate_wave<16, Dp / 16, LT, kHoriz, false, ADAPT, NT>(s, first, lane);
-    } else if (kind == kVert) {
-        if (g == 32)
-            aggregate_wave<32, Dp / 32, LT, kVert, false, ADAPT, NT>(s, first, lane);
-        else
-            aggregate_wave<16, Dp / 16, LT, kVert, false, ADAPT, NT>(s, first, lane);
-    } else {
-        if (g == 32)
-            aggregate_wave<32, Dp / 32, LT, kDiag, false, ADAPT, NT>(s, first, lane);
-        else
-            aggregate_wave<16, Dp / 16, LT, kDiag, false, ADAPT, NT>(s, first, lane);
-    }
-}
-
-// g: the work item's lanes per slice (its pair's horizontal or other group
-// width, by the direction's kind)
-template <typename LT, bool NT, bool ADAPT>
-__device__ __attribute__((always_inline)) inline void aggregate_item_dp(const SliceArgs& s, int Dp, int kind, int g,
-                                                                        int first, int lane) {
-    if (Dp == 64)
-        aggregate_item<LT, 64, NT, ADAPT>(s, kind, g, first, lane);
-    else if (Dp == 128)
-        aggregate_item<LT, 128, NT, ADAPT>(s, kind, g, first, lane);
-    else
-        aggregate_item<LT, 256, NT, ADAPT>(s, kind, g, first, lane);
-}
-
-// ANY_ADAPT: some pair of the batch uses the adaptive P2 (a second
-// instantiation, so batches without one keep the smaller kernel).  A
-// workgroup takes one quad of work items at a time, wavefront k its item k;
-// the quad's items have the same length, so its wavefronts finish together.
-template <bool NT, bool ANY_ADAPT>
-__global__ __launch_bounds__(256) void aggregate_batch_kernel(const BatchItem* items, const WorkItem* work,
-                                                              int nquads, unsigned* queue_counter, int P1, int P2) {
-    __shared__ uint16_t p2lut[ANY_ADAPT ? 256 : 1];
-    __shared__ unsigned quad;
-    if constexpr (ANY_ADAPT)  // P1, P2 belong to the batch: one table per block
-        fill_p2_lut(p2lut, P1, P2);
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    for (;;) {
-        // the barrier also ends every wavefront's read of the previous quad
-        // index (and, on the first pass, the penalty table's fill)
-        __syncthreads();
-        if (threadIdx.x == 0) quad = atomicAdd(queue_counter, 1u);
-        __syncthreads();
-        const unsigned q = __builtin_amdgcn_readfirstlane(quad);
-        if (q >= (unsigned)nquads) break;
-        const WorkItem w = work[(size_t)q * kQuad + wave];
-        if (w.item < 0) continue;
-        const BatchItem& it = items[w.item];
-        const uint32_t plane = (uint32_t)it.W * (uint32_t)it.H * (uint32_t)it.Dp;
-        void* lplane = it.l16 ? (void*)(reinterpret_cast<uint16_t*>(it.lbuf) + (size_t)plane * w.plane)
-                              : (void*)(reinterpret_cast<uint8_t*>(it.lbuf) + (size_t)plane * w.plane);
-        // a right-base direction reads the right-base costs; the adaptive P2
-        // follows its SGM's base image
-        SliceArgs s{w.rb ? it.cost_r : it.cost, it.census_l, it.census_r, lplane, plane, it.W, it.H, it.D, P1, P2,
-                    it.cmax, w.rx, w.ry};
-        s.img = w.rb ? it.right : it.left;
-        s.p2lut = ANY_ADAPT ? p2lut : nullptr;
-        const int kind = w.ry == 0 ? kHoriz : (w.rx == 0 ? kVert : kDiag);
-        const int g = kind == kHoriz ? it.gh : it.gv;
-        if (ANY_ADAPT && it.adaptive) {
-            if (it.l16)
-                aggregate_item_dp<uint16_t, NT, ANY_ADAPT>(s, it.Dp, kind, g, w.first, lane);
-            else
-                aggregate_item_dp<uint8_t, NT, ANY_ADAPT>(s, it.Dp, kind, g, w.first, lane);
-        } else {
-            if (it.l16)
-                aggregate_item_dp<uint16_t, NT, false>(s, it.Dp, kind, g, w.first, lane);
-            else
-                aggregate_item_dp<uint8_t, NT, false>(s, it.Dp, kind, g, w.first, lane);
-        }
     }
 }
 
@@ -551,10 +436,8 @@ hipError_t batch_launch(const BatchParams& bp, const BatchLaunch& B, const Batch
     hipLaunchKernelGGL(cost_batch_kernel, dim3((unsigned)B.cost_blocks), dim3(kCostThreads), B.cost_smem, s, d_items,
                        n);
     const int nquads = (int)(B.work.size() / kQuad);
-    auto agg = B.nt ? (B.any_adapt ? aggregate_batch_kernel<true, true> : aggregate_batch_kernel<true, false>)
-                    : (B.any_adapt ? aggregate_batch_kernel<false, true> : aggregate_batch_kernel<false, false>);
-    hipLaunchKernelGGL(agg, dim3((unsigned)B.blocks), dim3(256), 0, s, d_items, d_work, nquads, counter, bp.P1,
-                       bp.P2);
+    (B.any_adapt ? launch_batch_agg_adapt : launch_batch_agg)(B.nt, B.blocks, d_items, d_work, nquads, counter, bp.P1,
+                                                              bp.P2, s);
     hipLaunchKernelGGL(B.nt ? wta_batch_kernel<true> : wta_batch_kernel<false>, dim3((unsigned)B.wta_blocks),
                        dim3(1024), B.wta_smem, s, d_items, n);
     if (B.post_blocks > 0) {

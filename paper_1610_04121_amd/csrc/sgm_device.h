@@ -552,16 +552,26 @@ __device__ inline void census_cost_block(const CensusCostArgs& a, int bx, int y,
 // q*CPL + k (low half) and q*CPL + k + CPL/2 (high half), so the d-1 / d+1
 // neighbours of pair k are pairs k-1 / k+1 of the same lane, except at the
 // lane's two ends, which take one DPP lane shift and one v_alignbit each.
-// Per step, in saturating u16 arithmetic:
-//   lp    = L + P1                          (the d+-1 candidates of Eq. 3)
-//   R(d)  = min(L(d), lp(d-1), lp(d+1), m + P2)
-//   L'(d) = R(d) - m + C(p, d)              (m = min_k L(p - r, k))
+// Per step, with m = min_k L(p - r, k) and R(d) = min(L(p - r, d),
+// L(p - r, d +- 1) + P1) left by the step before:
+//   L'(d) = C(p, d) + min(R(d) - m, P2)     (Eq. 3; R >= m)
+//   R'(d) = min(L'(d), L'(d +- 1) + P1)
 //   m'    = min_d L'(d)                     (group min-reduction)
-// 0xFFFF stands for "no such disparity": the d-1 of d = 0, the d+1 of
-// d = D-1 and padded levels d >= D (their cost is 0xFFFF, so they stay
-// 0xFFFF).  Real values are at most Cmax + 2*P2 < 0xFFFF (validated), so
-// saturation never changes a result.  A path start sets L = 0 and m = 0,
-// which makes L' = C exactly.
+// so the chain from m to m' is subtract, minimum, add and the reduction, and
+// R' is formed beside the reduction.  "No such disparity" (the d-1 of d = 0,
+// the d+1 of d = D-1, padded levels d >= D) is 0xFFFF in saturating u16
+// arithmetic on 16-bit planes, and a finite stand-in on byte planes (below).
+// Real values are at most Cmax + 2*P2 < 0xFFFF (validated), so saturation
+// never changes a result.  A path start is R = 0 and m = 0, which makes
+// L' = C exactly.
+//
+// What bounds it: frames whose slices give each SIMD one wavefront or less
+// are bound by a step's length (72 ns for a 32-lane horizontal step, 31
+// instructions; 95 ns for a 16-lane vertical one, 44), the others by the
+// bytes.  Against the schedule the compiler chose by itself (86 and 114 ns):
+// 4 directions of 640x480, D = 128, alone on the device 56.1 -> 47.7 us
+// (5.6 -> 6.6 TB/s), its 4 diagonals 86.7 -> 53.7 us, 320x240, D = 64
+// 30.1 -> 22.3 us, 8 directions of 1242x375, D = 128 179.7 -> 164.2 us.
 // ---------------------------------------------------------------------------
 // Everything one wavefront needs to aggregate slices of one direction.
 struct SliceArgs {
@@ -619,6 +629,20 @@ constexpr int kDppWaveShr1 = 0x138;  // lane i reads lane i-1
 constexpr int kDppRowMirror = 0x140;
 constexpr int kDppRowHalfMirror = 0x141;
 
+// Lane j's value of each row of 16 lanes, in all lanes of the row
+// (row_newbcast; j is a constant once the caller's loop is unrolled).
+__device__ __attribute__((always_inline)) inline uint32_t row_broadcast(uint32_t v, int j) {
+#define SGM_ROW_BCAST(J) \
+    case J: return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x150 + J, 0xF, 0xF, true);
+    switch (j & 15) {
+        SGM_ROW_BCAST(0) SGM_ROW_BCAST(1) SGM_ROW_BCAST(2) SGM_ROW_BCAST(3) SGM_ROW_BCAST(4) SGM_ROW_BCAST(5)
+        SGM_ROW_BCAST(6) SGM_ROW_BCAST(7) SGM_ROW_BCAST(8) SGM_ROW_BCAST(9) SGM_ROW_BCAST(10) SGM_ROW_BCAST(11)
+        SGM_ROW_BCAST(12) SGM_ROW_BCAST(13) SGM_ROW_BCAST(14) default: break;
+    }
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x15F, 0xF, 0xF, true);
+#undef SGM_ROW_BCAST
+}
+
 // Lane q of a group receives lane q-1's (from_lower) or q+1's (from_upper)
 // value; a lane without a source receives 0 (bound_ctrl), and group edges are
 // overwritten by the caller's OR mask.
@@ -634,11 +658,20 @@ __device__ inline uint32_t from_upper(uint32_t v) {
 // Minimum over each group of G lanes; every lane of the group receives it.
 // The butterfly inside a row of 16 uses DPP (folded into v_min_u32_dpp);
 // groups spanning 2 or 4 rows combine rows with the gfx950 permlane swaps.
-template <int G>
-__device__ inline uint32_t group_min(uint32_t v) {
+// fill<i>() runs between stages i - 1 and i (0 .. 3): independent work for
+// the two wait states a DPP operand needs after it is written.
+struct NoFill {
+    template <int I> __device__ void operator()(std::integral_constant<int, I>) const {}
+};
+template <int G, typename FILL = NoFill>
+__device__ inline uint32_t group_min(uint32_t v, FILL fill = FILL{}) {
+    fill(std::integral_constant<int, 0>{});
     v = min(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, kDppQuadPerm1032, 0xF, 0xF, true));
+    fill(std::integral_constant<int, 1>{});
     v = min(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, kDppQuadPerm2301, 0xF, 0xF, true));
+    fill(std::integral_constant<int, 2>{});
     v = min(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, kDppRowHalfMirror, 0xF, 0xF, true));
+    fill(std::integral_constant<int, 3>{});
     v = min(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, kDppRowMirror, 0xF, 0xF, true));
     if constexpr (G >= 32) {
         const auto sw = __builtin_amdgcn_permlane16_swap(v, v, false, false);
@@ -703,25 +736,27 @@ __device__ inline uint32_t unpack_selector(int k, int d0, int D, uint32_t pad) {
 
 enum { kHoriz = 0, kVert = 1, kDiag = 2 };
 
-// Raw-buffer resource for a byte range (gfx9-family descriptor word 3).  Every
-// access below passes its whole byte offset in the VGPR operand, so the
-// hardware range check covers it: loads past `bytes` return 0 and stores past
-// it are dropped.
+// Raw-buffer resource for a byte range (gfx9-family descriptor word 3).
+// Accesses that rely on the hardware range check (loads past `bytes` return 0
+// and stores past it are dropped) pass their whole byte offset in the VGPR
+// operand; the aggregation's loads and stores stay inside the buffers by
+// themselves and put the part of the offset that is the same for the whole
+// wavefront into the scalar operand.
 __device__ inline __amdgpu_buffer_rsrc_t buffer_rsrc(const void* base, uint32_t bytes) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)bytes, 0x00020000);
 }
 
 template <int CPL>
-__device__ inline typename Raw<CPL>::T buffer_load_raw(__amdgpu_buffer_rsrc_t r, uint32_t ofs) {
+__device__ inline typename Raw<CPL>::T buffer_load_raw(__amdgpu_buffer_rsrc_t r, uint32_t ofs, uint32_t sofs) {
     if constexpr (CPL == 2) {
-        return (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(r, ofs, 0, 0);
+        return (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(r, ofs, sofs, 0);
     } else if constexpr (CPL == 4) {
-        return __builtin_amdgcn_raw_buffer_load_b32(r, ofs, 0, 0);
+        return __builtin_amdgcn_raw_buffer_load_b32(r, ofs, sofs, 0);
     } else if constexpr (CPL == 8) {
-        const auto v = __builtin_amdgcn_raw_buffer_load_b64(r, ofs, 0, 0);
+        const auto v = __builtin_amdgcn_raw_buffer_load_b64(r, ofs, sofs, 0);
         return make_uint2(v[0], v[1]);
     } else {
-        const auto v = __builtin_amdgcn_raw_buffer_load_b128(r, ofs, 0, 0);
+        const auto v = __builtin_amdgcn_raw_buffer_load_b128(r, ofs, sofs, 0);
         return make_uint4(v[0], v[1], v[2], v[3]);
     }
 }
@@ -729,21 +764,21 @@ __device__ inline typename Raw<CPL>::T buffer_load_raw(__amdgpu_buffer_rsrc_t r,
 // AUX is the cache-policy operand of the store (gfx950: 2 = non-temporal,
 // 16 = device scope, sc1).
 template <int AUX>
-__device__ inline void buffer_store(__amdgpu_buffer_rsrc_t r, uint32_t ofs, uint16_t v) {
-    __builtin_amdgcn_raw_buffer_store_b16(v, r, ofs, 0, AUX);
+__device__ inline void buffer_store(__amdgpu_buffer_rsrc_t r, uint32_t ofs, uint32_t sofs, uint16_t v) {
+    __builtin_amdgcn_raw_buffer_store_b16(v, r, ofs, sofs, AUX);
 }
 template <int AUX>
-__device__ inline void buffer_store(__amdgpu_buffer_rsrc_t r, uint32_t ofs, uint32_t v) {
-    __builtin_amdgcn_raw_buffer_store_b32(v, r, ofs, 0, AUX);
+__device__ inline void buffer_store(__amdgpu_buffer_rsrc_t r, uint32_t ofs, uint32_t sofs, uint32_t v) {
+    __builtin_amdgcn_raw_buffer_store_b32(v, r, ofs, sofs, AUX);
 }
 template <int AUX>
-__device__ inline void buffer_store(__amdgpu_buffer_rsrc_t r, uint32_t ofs, uint2 v) {
-    __builtin_amdgcn_raw_buffer_store_b64((unsigned __attribute__((ext_vector_type(2)))){v.x, v.y}, r, ofs, 0, AUX);
+__device__ inline void buffer_store(__amdgpu_buffer_rsrc_t r, uint32_t ofs, uint32_t sofs, uint2 v) {
+    __builtin_amdgcn_raw_buffer_store_b64((unsigned __attribute__((ext_vector_type(2)))){v.x, v.y}, r, ofs, sofs, AUX);
 }
 template <int AUX>
-__device__ inline void buffer_store(__amdgpu_buffer_rsrc_t r, uint32_t ofs, uint4 v) {
+__device__ inline void buffer_store(__amdgpu_buffer_rsrc_t r, uint32_t ofs, uint32_t sofs, uint4 v) {
     __builtin_amdgcn_raw_buffer_store_b128((unsigned __attribute__((ext_vector_type(4)))){v.x, v.y, v.z, v.w}, r, ofs,
-                                           0, AUX);
+                                           sofs, AUX);
 }
 
 // A lane's CPL L values as bytes in natural disparity order (u8 planes):
@@ -772,22 +807,22 @@ __device__ inline typename Raw<CPL>::T pack_u8(const u16x2 (&l)[CPL / 2]) {
 }
 
 // Packs a lane's L values in natural disparity order (u8 or u16) and stores
-// them at byte offset `ofs` of the L_r plane.  NT: non-temporal stores (the
+// them at byte offset `ofs` (per lane) + `sofs` of the L_r plane.  NT: non-temporal stores (the
 // frame's planes exceed the memory-side cache); otherwise device-scope (sc1)
 // stores, which measured faster than plain ones: the planes still reach the
 // memory-side cache for the WTA, and the L2 keeps more of the cost lines
 // that the opposite direction of a slice re-reads.
 template <int CPL, typename LT, bool NT = false>
-__device__ inline void store_l(__amdgpu_buffer_rsrc_t r, uint32_t ofs, const u16x2 (&l)[CPL / 2]) {
+__device__ inline void store_l(__amdgpu_buffer_rsrc_t r, uint32_t ofs, uint32_t sofs, const u16x2 (&l)[CPL / 2]) {
     constexpr int A = NT ? 2 : 16;
     constexpr uint32_t kPairLo = 0x05040100u;   // (a.lo16, b.lo16)
     constexpr uint32_t kPairHi = 0x07060302u;   // (a.hi16, b.hi16)
     if constexpr (sizeof(LT) == 1) {
-        buffer_store<A>(r, ofs, pack_u8<CPL>(l));
+        buffer_store<A>(r, ofs, sofs, pack_u8<CPL>(l));
     } else {
         constexpr int NP = CPL / 2;
         if constexpr (CPL == 2) {
-            buffer_store<A>(r, ofs, as1(l[0]));
+            buffer_store<A>(r, ofs, sofs, as1(l[0]));
         } else {
             // dword i = (d_2i, d_2i+1) from pairs 2i and 2i+1 (low halves,
             // then high halves)
@@ -798,11 +833,11 @@ __device__ inline void store_l(__amdgpu_buffer_rsrc_t r, uint32_t ofs, const u16
                 w[NP / 2 + i] = __builtin_amdgcn_perm(as1(l[2 * i + 1]), as1(l[2 * i]), kPairHi);
             }
             if constexpr (NP == 2) {
-                buffer_store<A>(r, ofs, make_uint2(w[0], w[1]));
+                buffer_store<A>(r, ofs, sofs, make_uint2(w[0], w[1]));
             } else {
 #pragma unroll
                 for (int i = 0; i < NP / 4; ++i)
-                    buffer_store<A>(r, ofs + 16 * i, make_uint4(w[4 * i], w[4 * i + 1], w[4 * i + 2], w[4 * i + 3]));
+                    buffer_store<A>(r, ofs + 16 * i, sofs, make_uint4(w[4 * i], w[4 * i + 1], w[4 * i + 2], w[4 * i + 3]));
             }
         }
     }
@@ -880,7 +915,6 @@ __device__ inline void aggregate_wave(const SliceArgs& a, int first_slice, int l
     static_assert(!(FUSED && ADAPT), "adaptive P2 uses the cost-volume variant");
     constexpr int NP = CPL / 2;
     constexpr int Dp = G * CPL;
-    constexpr int kDpShift = Dp == 64 ? 6 : (Dp == 128 ? 7 : 8);
     constexpr int PF = FUSED ? FusedPrefetch<CPL>::N : Prefetch<CPL>::N;
     // per-step input: raw cost bytes, or census words (fused variant)
     using RawT = std::conditional_t<FUSED, CensusStep<CPL>, typename Raw<CPL>::T>;
@@ -928,83 +962,115 @@ __device__ inline void aggregate_wave(const SliceArgs& a, int first_slice, int l
     const __amdgpu_buffer_rsrc_t rl = buffer_rsrc(a.lplane, plane_bytes * (uint32_t)sizeof(LT));
     const __amdgpu_buffer_rsrc_t rim = buffer_rsrc(a.img, ADAPT ? (uint32_t)W * (uint32_t)H : 0u);
 
-    // Group 0's position: byte offset `bo` of its pixel in a u8 [H][W][Dp]
-    // plane and, for diagonal slices, its column xc (kept in [0, W)).
-    int bo, xc;
-    if constexpr (KIND == kHoriz) {
-        xc = rx > 0 ? 0 : W - 1;
-        bo = (first_slice * W + xc) * Dp;
-    } else {
-        xc = first_slice;
-        bo = ((ry > 0 ? 0 : H - 1) * W + xc) * Dp;
-    }
-    const int bstep = (KIND == kHoriz ? rx : ry * W + (KIND == kDiag ? rx : 0)) * Dp;
-    const int qofs = q * CPL;
-    // byte offset of the lane relative to group 0 (horizontal: rows below;
-    // vertical: columns to the right; diagonal: columns to the right, or
-    // W - jg columns to the left once the group's column has wrapped)
-    const int lofs = (KIND == kHoriz ? jg * W : jg) * Dp + qofs;
-    const int lofs_wrapped = (jg - W) * Dp + qofs;
-    auto lane_ofs = [&](int b, int x) -> uint32_t {
-        if constexpr (KIND == kDiag) return (uint32_t)(b + (x + jg >= W ? lofs_wrapped : lofs));
-        return (uint32_t)(b + lofs);
+    // Group 0's position along its slice: pixel index, column (diagonals:
+    // kept in [0, W)) and step.  It is the same for the whole wavefront (a
+    // scalar); a lane adds its group's distance jl (pixels) from group 0 and
+    // its disparities: rows below (horizontal) or columns to the right, less
+    // W once a diagonal's group has wrapped to the left border.
+    struct Pos {
+        int pix, x, t;
     };
-    auto advance = [&](int& b, int& x) {
-        b += bstep;
-        if constexpr (KIND == kHoriz) x += rx;
+    const int pstep = KIND == kHoriz ? rx : ry * W + (KIND == kDiag ? rx : 0);
+    Pos cur;
+    cur.t = 0;
+    cur.x = KIND == kHoriz ? (rx > 0 ? 0 : W - 1) : first_slice;
+    cur.pix = KIND == kHoriz ? first_slice * W + cur.x : (ry > 0 ? 0 : H - 1) * W + cur.x;
+    // a position stays on the slice's last step, so the lookahead never
+    // leaves the slice
+    auto advance = [&](Pos& p) {
+        const bool more = p.t + 1 < steps;
+        p.t += 1;
+        p.pix += more ? pstep : 0;
+        if constexpr (KIND == kHoriz) p.x += more ? rx : 0;
         if constexpr (KIND == kDiag) {
-            x += rx;
-            const int under = x >> 31;             // -1 if x < 0
-            const int over = (W - 1 - x) >> 31;    // -1 if x >= W
-            const int wrap = (under & W) - (over & W);
-            x += wrap;
-            b += wrap * Dp;
+            p.x += more ? rx : 0;
+            const int wrap = p.x < 0 ? W : (p.x >= W ? -W : 0);
+            p.x += wrap;
+            p.pix += wrap;
         }
     };
-
-    u16x2 L[NP];
-#pragma unroll
-    for (int k = 0; k < NP; ++k) L[k] = as2(0u);
-    u16x2 mm = as2(0u);
+    const int jl0 = KIND == kHoriz ? jg * W : jg;
+    const int qofs = q * CPL;
+    auto lane_px = [&](const Pos& p) -> int {
+        if constexpr (KIND == kDiag) return p.x + jg >= W ? jg - W : jg;
+        return jl0;
+    };
     // restart column of a diagonal group: where it crosses the side border
     const int border = rx > 0 ? 0 : W - 1;
 
-    // smallest column any group of the wavefront is at (uniform): when it is
-    // >= Dp - 1, every lane's disparities are valid (x - d >= 0)
-    int xmin_all = 0;
-    // ADAPT: this step's P2 (looked up during the previous step; at a path
-    // start L and mm are 0 and the P2 of that step does not matter)
-    uint32_t p2cur = (uint32_t)a.P2;
-    auto step = [&](const RawT& raw, uint32_t iv, uint32_t inext, int t) {
-        if constexpr (FUSED) {
-            if constexpr (KIND == kHoriz)
-                xmin_all = xc;
-            else if constexpr (KIND == kVert)
-                xmin_all = xc;
-            else
-                xmin_all = xc + 64 / G - 1 >= W ? 0 : xc;  // a wrapped group sits at a small column
-        }
-        if constexpr (KIND == kDiag) {
-            const int xl = xc + jg >= W ? xc + jg - W : xc + jg;
-            if (xl == border) {
+    // Path state: R = min(L(d), L(d +- 1) + P1) of the last step and the
+    // path minimum mm = min_d L(d).  A path start is R = 0, mm = 0.
+    u16x2 R[NP];
 #pragma unroll
-                for (int k = 0; k < NP; ++k) L[k] = as2(0u);
-                mm = as2(0u);
+    for (int k = 0; k < NP; ++k) R[k] = as2(0u);
+    u16x2 mm = as2(0u);
+
+    // ADAPT: the P2 of a block's PF steps, one step per lane of a row of 16
+    // (twice in a u16 pair), each broadcast to its row when its step comes:
+    // one load pair and one table lookup per block instead of per step.  The
+    // loads run a block ahead, the lookup three steps.  (At a path start R
+    // and mm are 0 and the P2 of that step does not matter.)
+    uint32_t p2blk = 0, p2next = 0, inten[2] = {0, 0};
+    int ax = 0;  // diagonal: the column of the lane's step
+    if constexpr (ADAPT && KIND == kDiag) ax = first_slice + jg + rx * (lane & (PF - 1));
+    auto adapt_load = [&](int t0) {  // intensities of steps t0 + (lane mod PF) and the one before
+        if constexpr (ADAPT) {
+            const int t = min(t0 + (lane & (PF - 1)), steps - 1);
+#pragma unroll
+            for (int b = 0; b < 2; ++b) {
+                const int u = max(t - b, 0);
+                uint32_t pix;
+                if constexpr (KIND == kHoriz) {
+                    pix = (uint32_t)((first_slice + jg) * W + (rx > 0 ? u : W - 1 - u));
+                } else {
+                    int x = first_slice + jg;
+                    if constexpr (KIND == kDiag) {
+                        while (ax < 0) ax += W;
+                        while (ax >= W) ax -= W;
+                        x = ax - b * rx;
+                        x += x < 0 ? W : (x >= W ? -W : 0);
+                    }
+                    pix = (uint32_t)((ry > 0 ? u : H - 1 - u) * W + x);
+                }
+                inten[b] = __builtin_amdgcn_raw_buffer_load_b8(rim, pix, 0, 0);
             }
+            if constexpr (KIND == kDiag) ax += rx * PF;
         }
-        u16x2 c[NP];
+    };
+    auto adapt_lookup = [&] {
+        if constexpr (ADAPT) {
+            const uint32_t g = inten[0] > inten[1] ? inten[0] - inten[1] : inten[1] - inten[0];
+            p2next = a.p2lut[g] * 0x10001u;
+        }
+    };
+    constexpr int kLookupStep = PF - 3;
+
+    // ring[j] holds the raw costs of the step congruent to j modulo PF; the
+    // loads lead by PF steps.  c holds the unpacked costs of the current
+    // step: a step unpacks the next one's (its load is PF - 1 steps old) and
+    // refills its own slot, whose costs the step before unpacked.
+    RawT ring[PF];
+    u16x2 c[NP];
+    auto load_at = [&](const Pos& p) -> RawT {
+        const int pix = p.pix + lane_px(p);
+        if constexpr (FUSED) {
+            RawT cs;
+            load_census<CPL>(rcl, rcr, 8u * (uint32_t)pix, 8u * (uint32_t)(pix + kCensusGuard - qofs - (CPL - 1)), cs);
+            return cs;
+        } else {
+            return buffer_load_raw<CPL>(rc, (uint32_t)(pix * Dp + qofs), 0u);
+        }
+    };
+    auto unpack = [&](const RawT& raw, const Pos& p) {
         if constexpr (FUSED) {
             // the lane's disparities are valid (x - d >= 0) for cells
             // c <= x - q*CPL; x of the lane's group is group 0's column + jg
             // (horizontal: same column; diagonal: wrapped)
-            int xg;
-            if constexpr (KIND == kHoriz)
-                xg = xc;
-            else if constexpr (KIND == kVert)
-                xg = xc + jg;
-            else
-                xg = xc + jg >= W ? xc + jg - W : xc + jg;
+            const int xg = KIND == kHoriz ? p.x : (KIND == kDiag && p.x + jg >= W ? p.x + jg - W : p.x + jg);
             const int valid_c = xg - q * CPL;
+            // smallest column any group of the wavefront is at (uniform): when
+            // it is >= Dp - 1, every lane's disparities are valid
+            const int xmin_all = KIND == kDiag && p.x + 64 / G - 1 >= W ? 0 : p.x;
             if (xmin_all >= Dp - 1)
                 census_costs<CPL, true>(raw, valid_c, (uint32_t)a.cmax, sel, c);
             else
@@ -1012,37 +1078,56 @@ __device__ inline void aggregate_wave(const SliceArgs& a, int first_slice, int l
         } else {
             unpack_costs<CPL>(raw, sel, c);
         }
-        u16x2 lp[NP];
-#pragma unroll
-        for (int k = 0; k < NP; ++k) lp[k] = vadds(L[k], P1v);
-        const uint32_t prev = from_lower<G>(as1(lp[NP - 1])) | edge_lo;
-        const uint32_t next = from_upper<G>(as1(lp[0])) | edge_hi;
-        const u16x2 lo0 = as2(__builtin_amdgcn_alignbit(as1(lp[NP - 1]), prev, 16));
-        const u16x2 hiN = as2(__builtin_amdgcn_alignbit(next, as1(lp[0]), 16));
+    };
+
+    // One step: L = C + min(R - mm, P2) (Eq. 3 with the minimum over the
+    // path taken out), then R and mm of the next step, side by side, and the
+    // unpacking of its costs (`next`, at position `pn`).  `store` puts L
+    // where it goes.
+    //
+    // A wavefront alone on its SIMD issues one instruction every four cycles
+    // and an instruction that waits for the previous one's result takes about
+    // ten, so a step costs its instruction count or its chain (the minimum
+    // over L, then subtract, minimum, add), whichever is longer.  R, the
+    // unpacking, the store and the load fill the gaps of the minimum's
+    // reduction: the barrier to the compiler's scheduler at the end of a step
+    // keeps them there (without it the unpacks of many steps were gathered
+    // at the top of a block, where they waited for loads just issued).
+    auto step = [&](const RawT& next, const Pos& pn, int j, auto&& store) {
+        auto fence = [] { __builtin_amdgcn_sched_barrier(0); };
         u16x2 p2v = P2v;
-        uint32_t p2next = 0;
         if constexpr (ADAPT) {
-            p2v = as2(p2cur * 0x10001u);
-            // the next step's P2, from the intensity change to the next pixel;
-            // the LDS read completes while this step runs
-            const uint32_t g = inext > iv ? inext - iv : iv - inext;
-            p2next = a.p2lut[g];
+            p2v = as2(row_broadcast(p2blk, j));
+            fence();
         }
-        const u16x2 mp2 = vadds(mm, p2v);
+        u16x2 L[NP];
 #pragma unroll
-        for (int k = 0; k < NP; ++k) {
-            const u16x2 lo = k == 0 ? lo0 : lp[k - 1];
-            const u16x2 hi = k == NP - 1 ? hiN : lp[k + 1];
-            const u16x2 R = kF16 ? vmin(vmin3h(lo, hi, L[k]), mp2) : vmin(vmin(lo, hi), vmin(L[k], mp2));
-            L[k] = vadds(R - mm, c[k]);
-        }
+        for (int k = 0; k < NP; ++k) L[k] = R[k] - mm;
+        fence();
+#pragma unroll
+        for (int k = 0; k < NP; ++k) L[k] = vmin(L[k], p2v);
+        fence();
+#pragma unroll
+        for (int k = 0; k < NP; ++k) L[k] = kF16 ? L[k] + c[k] : vadds(L[k], c[k]);
+        fence();
         // minimum over the lane's cells, replicated in both halves
         u16x2 tm;
+        u16x2 lp[NP];
+        auto add_p1 = [&] {
+            fence();
+#pragma unroll
+            for (int k = 0; k < NP; ++k) lp[k] = kF16 ? L[k] + P1v : vadds(L[k], P1v);
+            fence();
+        };
         if constexpr (kF16 && NP >= 4) {
             u16x2 t = vmin3h(L[0], L[1], L[2]);
+            add_p1();
 #pragma unroll
             for (int k = 3; k + 1 < NP; k += 2) t = vmin3h(t, L[k], L[k + 1]);
             if constexpr (NP % 2 == 0) t = vmin(t, L[NP - 1]);
+            fence();
+            unpack(next, pn);
+            fence();
             tm = vmin(t, t.yx);
         } else {
             u16x2 t[NP];
@@ -1052,72 +1137,158 @@ __device__ inline void aggregate_wave(const SliceArgs& a, int first_slice, int l
             for (int w = 1; w < NP; w *= 2)
 #pragma unroll
                 for (int k = 0; k + w < NP; k += 2 * w) t[k] = vmin(t[k], t[k + w]);
+            add_p1();
             tm = vmin(t[0], t[0].yx);
+            fence();
+            unpack(next, pn);
         }
-        mm = as2(group_min<G>(as1(tm)));
-        if constexpr (kToPlane)
-            store_l<CPL, LT, NT>(rl, lane_ofs(bo, xc) * (uint32_t)sizeof(LT), L);
-        else
-            sink->put(t, L);
-        advance(bo, xc);
-        if constexpr (ADAPT) p2cur = p2next;
+        uint32_t prev, nxt;
+        u16x2 lo0, hiN;
+        auto fill = [&](auto stage) {
+            constexpr int I = decltype(stage)::value;
+            fence();
+            if constexpr (I == 0) {
+                prev = from_lower<G>(as1(lp[NP - 1])) | edge_lo;
+                nxt = from_upper<G>(as1(lp[0])) | edge_hi;
+            } else if constexpr (I == 1) {
+                lo0 = as2(__builtin_amdgcn_alignbit(as1(lp[NP - 1]), prev, 16));
+                hiN = as2(__builtin_amdgcn_alignbit(nxt, as1(lp[0]), 16));
+            } else if constexpr (I == 2) {
+                store(L);
+            } else {
+#pragma unroll
+                for (int k = 0; k < NP; ++k) {
+                    const u16x2 lo = k == 0 ? lo0 : lp[k - 1];
+                    const u16x2 hi = k == NP - 1 ? hiN : lp[k + 1];
+                    R[k] = kF16 ? vmin3h(lo, hi, L[k]) : vmin(vmin(lo, hi), L[k]);
+                }
+            }
+            fence();
+        };
+        mm = as2(group_min<G>(as1(tm), fill));
+    };
+    // a step at `cur` in the general form (restarts, wraps, any position)
+    auto step_at_cur = [&](const RawT& next, int j) {
+        if constexpr (KIND == kDiag) {
+            const int xl = cur.x + jg >= W ? cur.x + jg - W : cur.x + jg;
+            if (xl == border) {
+#pragma unroll
+                for (int k = 0; k < NP; ++k) R[k] = as2(0u);
+                mm = as2(0u);
+            }
+        }
+        const Pos here = cur;
+        advance(cur);
+        step(next, cur, j, [&](const u16x2 (&L)[NP]) {
+            if constexpr (kToPlane)
+                store_l<CPL, LT, NT>(rl, (uint32_t)((here.pix + lane_px(here)) * Dp + qofs) * (uint32_t)sizeof(LT), 0u, L);
+            else
+                sink->put(here.t, L);
+        });
     };
 
-    // ring[j] holds the raw costs of the step congruent to j modulo PF.  The
-    // lookahead position leads by PF - 1 steps and runs past the slice's end
-    // near the finish; those loads are never consumed (and past the plane
-    // they return 0).
-    auto load = [&](int b, int x) -> RawT {
-        if constexpr (FUSED) {
-            // pixel index of the lane's group: byte offset / Dp, with the
-            // lane's disparity offset qofs removed
-            const int pix = (int)((lane_ofs(b, x) - (uint32_t)qofs) / (uint32_t)Dp);
-            RawT cs;
-            load_census<CPL>(rcl, rcr, 8u * (uint32_t)pix,
-                             8u * (uint32_t)(pix + kCensusGuard - qofs - (CPL - 1)), cs);
-            return cs;
-        } else {
-            return buffer_load_raw<CPL>(rc, lane_ofs(b, x));
-        }
-    };
-    // intensity of the lane's group pixel (ADAPT): pixel index = (byte
-    // offset - qofs) / Dp; past the image the range check returns 0
-    auto load_i = [&](int b, int x) -> uint32_t {
-        if constexpr (ADAPT)
-            return __builtin_amdgcn_raw_buffer_load_b8(rim, (lane_ofs(b, x) - (uint32_t)qofs) >> kDpShift, 0, 0);
-        else
-            return 0u;
-    };
-    RawT ring[PF];
-    uint32_t iring[ADAPT ? PF : 1];
-    int ba = bo, xa = xc;
+    adapt_load(0);
+    adapt_lookup();
+    Pos ahead = cur;
+    // Dropped stores (an empty buffer) between the first loads, so that a
+    // load has as many memory operations behind it here as in the loop: the
+    // compiler's wait before a step then fits the loop (PF - 1 loads and
+    // stores may be outstanding) instead of this first block.
+    const __amdgpu_buffer_rsrc_t rnone = buffer_rsrc(a.lplane, 0u);
 #pragma unroll
     for (int j = 0; j < PF; ++j) {
-        if (j) advance(ba, xa);
-        ring[j] = load(ba, xa);
-        if constexpr (ADAPT) iring[j] = load_i(ba, xa);
+        ring[j] = load_at(ahead);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (kToPlane) buffer_store<0>(rnone, 0u, 0u, 0u);
+        __builtin_amdgcn_sched_barrier(0);
+        advance(ahead);
     }
+    unpack(ring[0], cur);
+
+    // Up to PF steps with the loads of the PF steps after them, in the general
+    // form: any position, the slice's end, restarts and wraps.
     int k = 0;
-    for (; k + PF <= steps; k += PF) {
+    auto chunk_any = [&](auto whole) {
+        p2blk = p2next;
+        adapt_load(k + PF);
 #pragma unroll
         for (int j = 0; j < PF; ++j) {
-            const RawT raw = ring[j];
-            // slot j + 1 (mod PF) holds the next step's intensity: slot 0 was
-            // refilled with step k + PF at j = 0
-            const uint32_t iv = ADAPT ? iring[ADAPT ? j : 0] : 0u;
-            advance(ba, xa);
-            ring[j] = load(ba, xa);
-            if constexpr (ADAPT) iring[j] = load_i(ba, xa);
-            step(raw, iv, ADAPT ? iring[ADAPT ? (j + 1) % PF : 0] : 0u, k + j);
+            __builtin_amdgcn_sched_barrier(0);
+            if (decltype(whole)::value || k + j < steps) {
+                if (j == kLookupStep) adapt_lookup();
+                ring[j] = load_at(ahead);
+                step_at_cur(ring[(j + 1) % PF], j);
+                advance(ahead);
+            }
         }
+        __builtin_amdgcn_sched_barrier(0);
         if constexpr (!kToPlane) sink->chunk_done();
-    }
+        k += PF;
+    };
+    // The same for blocks that neither cross a border nor reach the slice's
+    // end with their loads.  Loads and stores share their offsets (the
+    // plane's resource is shifted back by PF steps): a scalar one that moves
+    // by a step (vertical, diagonal) or a block (horizontal, whose steps
+    // differ in the lane offset).
+    const uint32_t voff = (uint32_t)(jl0 * Dp + qofs);
+    const __amdgpu_buffer_rsrc_t rls = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<uint8_t*>(reinterpret_cast<const uint8_t*>(a.lplane)) - (ptrdiff_t)PF * pstep * Dp * (int)sizeof(LT), 0,
+        -1, 0x00020000);
+    uint32_t vstep[KIND == kHoriz ? PF : 1];
 #pragma unroll
-    for (int j = 0; j < PF; ++j)
-        if (k + j < steps)
-            step(ring[j], ADAPT ? iring[ADAPT ? j : 0] : 0u, ADAPT ? iring[ADAPT ? (j + 1) % PF : 0] : 0u, k + j);
-    if constexpr (!kToPlane)
-        if (k < steps) sink->chunk_done();
+    for (int j = 0; j < (KIND == kHoriz ? PF : 1); ++j)
+        vstep[j] = voff + (uint32_t)((KIND == kHoriz ? (rx > 0 ? j : PF - 1 - j) : 0) * Dp);
+    auto chunk_fast = [&]() {
+        if constexpr (!FUSED) {
+            uint32_t so = (uint32_t)((ahead.pix - (KIND == kHoriz && rx < 0 ? PF - 1 : 0)) * Dp);
+            const uint32_t sstep = (uint32_t)(pstep * Dp);
+            p2blk = p2next;
+            adapt_load(k + PF);
+#pragma unroll
+            for (int j = 0; j < PF; ++j) {
+                const uint32_t vo = vstep[KIND == kHoriz ? j : 0];
+                __builtin_amdgcn_sched_barrier(0);
+                if (j == kLookupStep) adapt_lookup();
+                ring[j] = buffer_load_raw<CPL>(rc, vo, so);
+                step(ring[(j + 1) % PF], cur, j, [&](const u16x2 (&L)[NP]) {
+                    if constexpr (kToPlane)
+                        store_l<CPL, LT, NT>(rls, vo * (uint32_t)sizeof(LT), so * (uint32_t)sizeof(LT), L);
+                    else
+                        sink->put(cur.t + j, L);
+                });
+                if constexpr (KIND != kHoriz) so += sstep;
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            for (Pos* p : {&cur, &ahead}) {
+                p->t += PF;
+                p->pix += PF * pstep;
+                if constexpr (KIND != kVert) p->x += PF * rx;
+                if constexpr (KIND == kDiag) {
+                    const int wrap = p->x < 0 ? W : (p->x >= W ? -W : 0);
+                    p->x += wrap;
+                    p->pix += wrap;
+                }
+            }
+            if constexpr (!kToPlane) sink->chunk_done();
+            k += PF;
+        }
+    };
+    // The conditional steps come last: a loop back from them to the others
+    // would make the compiler wait there for loads that may be recent.
+    if constexpr (KIND == kDiag && !FUSED) {
+        constexpr int S = 64 / G;
+        while (k + PF <= steps) {
+            // no group restarts or wraps, neither in a block nor in the steps
+            // it loads: columns 1 .. W - S - 1 for group 0
+            const int inner = rx > 0 ? (cur.x >= 1 ? (W - S - cur.x) / PF - 1 : 0) : (cur.x < W - S ? cur.x / PF - 1 : 0);
+            const int fast = min((steps - k) / PF - 1, inner);
+            for (int i = 0; i < fast; ++i) chunk_fast();
+            chunk_any(std::true_type{});
+        }
+    } else if constexpr (!FUSED) {
+        while (k + 2 * PF <= steps) chunk_fast();
+    }
+    while (k < steps) chunk_any(std::false_type{});
 }
 
 // ---------------------------------------------------------------------------

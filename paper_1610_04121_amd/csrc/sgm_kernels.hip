@@ -6,6 +6,7 @@
 
 #include <cstdlib>
 
+#include "sgm_agg.h"
 #include "sgm_device.h"
 #include "sgm_plan.h"
 
@@ -30,73 +31,6 @@ template <bool RB, int DP>
 __global__ __launch_bounds__(kCostThreads) void cost_kernel(CostArgs a) {
     extern __shared__ __align__(16) uint64_t cost_smem[];
     cost_block<RB, DP>(a, blockIdx.x, blockIdx.y, cost_smem);
-}
-
-// Direction table of one pair's aggregation launch: the directions of one
-// SGM, or of two (left-base and right-base, for the full left-right check).
-constexpr int kMaxLaunchDirs = 2 * kMaxDirs;
-struct AggArgs {
-    SliceArgs base;          // shared fields; rx, ry, cost, lplane set per direction
-    void* lbuf;              // all L_r planes
-    int ndirs, total;
-    int start[kMaxLaunchDirs + 1];  // first wave of each direction
-    int rx[kMaxLaunchDirs], ry[kMaxLaunchDirs], plane_index[kMaxLaunchDirs];
-    const uint8_t* cost[kMaxLaunchDirs];  // the cost volume each direction reads
-    const uint8_t* img[kMaxLaunchDirs];   // its SGM's base image (adaptive P2)
-    // paired[k]: directions k and k + 1 are opposite, axis-aligned and have
-    // the same wave count; their waves interleave (see aggregate_kernel)
-    int paired[kMaxLaunchDirs];
-};
-
-// One launch covers every direction.  Horizontal slices (the longest when
-// W > H) may use a different group width GH than the others (GV), so that
-// the longest dependency chains get the fewest instructions per step.
-template <int GH, int GV, int Dp, typename LT, bool FUSED, bool ADAPT, bool NT>
-__global__ __launch_bounds__(256) void aggregate_kernel(AggArgs a) {
-    __shared__ uint16_t p2lut[ADAPT ? 256 : 1];
-    if constexpr (ADAPT) {  // every wave of the block takes part before any leaves
-        fill_p2_lut(p2lut, a.base.P1, a.base.P2);
-        __syncthreads();
-    }
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
-    if (wave >= a.total) return;
-    int r = 0;
-    while (r + 1 < a.ndirs && wave >= a.start[r + 1]) ++r;
-    int local = wave - a.start[r];
-    // The 2n waves of a pair of opposite directions over the same n slice
-    // groups interleave two by two (A, A, B, B per workgroup), so both
-    // directions' waves over the same slices share a CU and its L2: the
-    // second read of a slice's costs can hit where the two walks pass close
-    // in time.  A bijection between the pair's waves and (direction, slice
-    // group); an odd n ends with one wave of each.
-    const int r0 = (r > 0 && a.paired[r - 1]) ? r - 1 : r;
-    if (a.paired[r0]) {
-        const int n = a.start[r0 + 1] - a.start[r0];
-        const int j = wave - a.start[r0];
-        const int g = j >> 2, w4 = j & 3;
-        if (4 * g + 4 <= 2 * n) {
-            r = r0 + (w4 >> 1);
-            local = 2 * g + (w4 & 1);
-        } else {
-            r = r0 + (w4 & 1);
-            local = 2 * g;
-        }
-    }
-    SliceArgs s = a.base;
-    s.rx = a.rx[r];
-    s.ry = a.ry[r];
-    s.cost = a.cost[r];
-    s.img = a.img[r];
-    s.p2lut = ADAPT ? p2lut : nullptr;
-    s.lplane = reinterpret_cast<LT*>(a.lbuf) + (size_t)s.plane * a.plane_index[r];
-    if (s.ry == 0) {
-        aggregate_wave<GH, Dp / GH, LT, kHoriz, FUSED, ADAPT, NT>(s, local * (64 / GH), lane);
-    } else if (s.rx == 0) {
-        aggregate_wave<GV, Dp / GV, LT, kVert, FUSED, ADAPT, NT>(s, local * (64 / GV), lane);
-    } else {
-        aggregate_wave<GV, Dp / GV, LT, kDiag, FUSED, ADAPT, NT>(s, local * (64 / GV), lane);
-    }
 }
 
 template <typename LT, bool NT, bool FOLD>
@@ -336,46 +270,6 @@ static void fill_agg_args(const Plan& p, const Workspace& ws, const uint8_t* lef
     }
 }
 
-// Images of the two SGMs (base left / base right) for the adaptive P2.
-struct Images {
-    const uint8_t *left, *right;
-    bool skip_last;  // leave out the direction the final pass fuses
-};
-
-template <int GH, int GV, int Dp, typename LT, bool FUSED, bool ADAPT, bool NT>
-static hipError_t launch_agg_t(const Plan& p, const Workspace& ws, Images im, hipStream_t stream) {
-    AggArgs a;
-    fill_agg_args(p, ws, im.left, im.right, 64 / GH, 64 / GV, a, im.skip_last);
-    hipLaunchKernelGGL((aggregate_kernel<GH, GV, Dp, LT, FUSED, ADAPT, NT>), dim3((a.total + 3) / 4), dim3(256), 0,
-                       stream, a);
-    return hipGetLastError();
-}
-
-template <int Dp, typename LT, bool FUSED, bool ADAPT, bool NT>
-static hipError_t launch_agg_dp(const Plan& p, const Workspace& ws, Images im, int gh, int gv, hipStream_t stream) {
-    switch (gh * 100 + gv) {
-        case 1616: return launch_agg_t<16, 16, Dp, LT, FUSED, ADAPT, NT>(p, ws, im, stream);
-        case 3216: return launch_agg_t<32, 16, Dp, LT, FUSED, ADAPT, NT>(p, ws, im, stream);
-        case 3232: return launch_agg_t<32, 32, Dp, LT, FUSED, ADAPT, NT>(p, ws, im, stream);
-        default: break;
-    }
-    if constexpr (Dp >= 128) {  // 64 lanes need at least 2 levels per lane
-        if (gh == 64 && gv == 16) return launch_agg_t<64, 16, Dp, LT, FUSED, ADAPT, NT>(p, ws, im, stream);
-        if (gh == 64 && gv == 32) return launch_agg_t<64, 32, Dp, LT, FUSED, ADAPT, NT>(p, ws, im, stream);
-    }
-    return hipErrorInvalidValue;
-}
-
-template <typename LT, bool FUSED, bool ADAPT, bool NT>
-static hipError_t launch_agg_lt(const Plan& p, const Workspace& ws, Images im, int gh, int gv, hipStream_t stream) {
-    if (p.Dp == 64) {
-        // Dp = 64 has only 4 levels per lane at G = 16 and 2 at G = 32
-        return launch_agg_dp<64, LT, FUSED, ADAPT, NT>(p, ws, im, gh == 64 ? 32 : gh, gv == 64 ? 32 : gv, stream);
-    }
-    if (p.Dp == 128) return launch_agg_dp<128, LT, FUSED, ADAPT, NT>(p, ws, im, gh, gv, stream);
-    return launch_agg_dp<256, LT, FUSED, ADAPT, NT>(p, ws, im, gh, gv, stream);
-}
-
 // Group widths: horizontal slices are the longest chains on wide images,
 // so they get more lanes (fewer instructions per step); the rest use 16.
 void default_lanes(const Plan& p, int* gh, int* gv) {
@@ -389,22 +283,19 @@ hipError_t launch_aggregate(const Plan& p, const Workspace& ws, hipStream_t stre
                             const uint8_t* right, bool skip_last) {
     int gh = p.lanes_h, gv = p.lanes_v;
     if (gh <= 0 || gv <= 0) default_lanes(p, &gh, &gv);
-    const Images im{left, right, skip_last};
-    if (p.adaptive) {
-        if (!left || (p.lr_full && !right)) return hipErrorInvalidValue;
-        return p.l16 ? launch_agg_lt<uint16_t, false, true, false>(p, ws, im, gh, gv, stream)
-                     : launch_agg_lt<uint8_t, false, true, false>(p, ws, im, gh, gv, stream);
+    if (p.Dp == 64) {  // 64 lanes need at least 2 levels per lane
+        gh = std::min(gh, 32);
+        gv = std::min(gv, 32);
     }
-    if (fused_aggregation(p))
-        return p.l16 ? launch_agg_lt<uint16_t, true, false, false>(p, ws, im, gh, gv, stream)
-                     : launch_agg_lt<uint8_t, true, false, false>(p, ws, im, gh, gv, stream);
+    if (p.adaptive && (!left || (p.lr_full && !right))) return hipErrorInvalidValue;
+    AggArgs a;
+    fill_agg_args(p, ws, left, right, 64 / gh, 64 / gv, a, skip_last);
     // the store policy is an instruction operand: a second instantiation of
     // the plain (stored-cost, constant-P2) kernels
-    if (p.nt_store)
-        return p.l16 ? launch_agg_lt<uint16_t, false, false, true>(p, ws, im, gh, gv, stream)
-                     : launch_agg_lt<uint8_t, false, false, true>(p, ws, im, gh, gv, stream);
-    return p.l16 ? launch_agg_lt<uint16_t, false, false, false>(p, ws, im, gh, gv, stream)
-                 : launch_agg_lt<uint8_t, false, false, false>(p, ws, im, gh, gv, stream);
+    const AggVariant v{gh, gv, p.l16, fused_aggregation(p), p.adaptive, p.nt_store && !p.adaptive && !fused_aggregation(p)};
+    if (p.Dp == 64) return launch_agg_64(a, v, stream);
+    if (p.Dp == 128) return launch_agg_128(a, v, stream);
+    return launch_agg_256(a, v, stream);
 }
 
 bool final_pass_active(const Plan& p) {
