@@ -24,6 +24,9 @@ struct AggArgs {
     // paired[k]: directions k and k + 1 are opposite, axis-aligned and have
     // the same wave count; their waves interleave (see aggregate_kernel)
     int paired[kMaxLaunchDirs];
+    // the horizontal directions keep only the columns the row kernel enters
+    // its segments from (CkptSink)
+    int ckpt;
 };
 
 // Which instantiation of the aggregation kernel to launch.

@@ -53,6 +53,12 @@ __global__ __launch_bounds__(256) void aggregate_kernel(AggArgs a) {
     s.p2lut = ADAPT ? p2lut : nullptr;
     s.lplane = reinterpret_cast<LT*>(a.lbuf) + (size_t)s.plane * a.plane_index[r];
     if (s.ry == 0) {
+        if constexpr (!FUSED) {
+            if (a.ckpt) {
+                aggregate_wave<GH, Dp / GH, LT, kHoriz, FUSED, ADAPT, NT, CkptSink>(s, local * (64 / GH), lane);
+                return;
+            }
+        }
         aggregate_wave<GH, Dp / GH, LT, kHoriz, FUSED, ADAPT, NT>(s, local * (64 / GH), lane);
     } else if (s.rx == 0) {
         aggregate_wave<GV, Dp / GV, LT, kVert, FUSED, ADAPT, NT>(s, local * (64 / GV), lane);

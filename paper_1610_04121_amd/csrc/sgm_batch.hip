@@ -25,26 +25,13 @@
 #include "sgm_batch_agg.h"
 #include "sgm_device.h"
 #include "sgm_plan.h"
+#include "sgm_row.h"
 
 namespace sgm {
 
 namespace {
 
 using namespace dev;
-
-// Index of the pair whose block range [blk0, next blk0) holds block b.
-template <int BatchItem::*FIRST>
-__device__ inline int find_item(const BatchItem* items, int n, int b) {
-    int lo = 0, hi = n;  // items[lo].*FIRST <= b < items[hi].*FIRST
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (items[mid].*FIRST <= b)
-            lo = mid;
-        else
-            hi = mid;
-    }
-    return lo;
-}
 
 __global__ __launch_bounds__(256) void census_batch_kernel(const BatchItem* items, int n, int generic, int rx,
                                                            int ry, unsigned* queue_counter) {
@@ -91,32 +78,6 @@ __global__ __launch_bounds__(kCostThreads) void cost_batch_kernel(const BatchIte
         local -= nx * it.H;
         cost_batch_block<true>(it, local % nx, local / nx, cost_smem);
     }
-}
-
-// Blocks 0 .. H - 1 of a pair are its rows; with the full left-right check
-// blocks H .. 2H - 1 are the rows of the right-base SGM, whose winners are
-// D_R.
-template <bool NT>
-__global__ __launch_bounds__(1024) void wta_batch_kernel(const BatchItem* items, int n) {
-    extern __shared__ uint32_t wta_smem[];
-    const int b = blockIdx.x;
-    const BatchItem& it = items[find_item<&BatchItem::wta_blk0>(items, n, b)];
-    const bool post = it.median || it.lrcheck;
-    const size_t plane = (size_t)it.W * it.H * it.Dp;
-    int y = b - it.wta_blk0;
-    WtaArgs a{it.lbuf, plane, post ? it.dl : it.out, (it.lrcheck && !it.lr_full) ? it.dr : nullptr,
-              it.W, it.H, it.D, it.Dp, it.P, it.subpixel};
-    if (y >= it.H) {  // right-base rows: planes P .. 2P - 1, winners into D_R
-        y -= it.H;
-        a.lbuf = static_cast<const uint8_t*>(it.lbuf) + plane * it.P * (it.l16 ? 2 : 1);
-        a.dl = it.dr;
-        a.dr = nullptr;
-        a.subpixel = 0;
-    }
-    if (it.l16)
-        wta_row<uint16_t, NT>(a, y, wta_smem);
-    else
-        wta_row<uint8_t, NT>(a, y, wta_smem);
 }
 
 __global__ __launch_bounds__(256) void post_batch_kernel(const BatchItem* items, int n) {
@@ -269,8 +230,17 @@ int grow_staging(BatchStaging* b, size_t nitems, size_t nwork) {
 struct BatchLaunch {
     std::vector<BatchItem> desc;
     std::vector<WorkItem> work;
-    size_t census_blocks = 0, cost_blocks = 0, wta_blocks = 0, post_blocks = 0;
-    size_t cost_smem = 0, wta_smem = 0, post_smem = 0;
+    size_t census_blocks = 0, cost_blocks = 0, post_blocks = 0;
+    size_t cost_smem = 0, post_smem = 0;
+    // The row kernel is one launch per variant (padded range, path count,
+    // plane type): pairs of a variant follow each other in desc.
+    struct Rows {
+        int Dp, first, n;  // pairs desc[first .. first + n)
+        RowVariant v;
+        size_t blocks, smem;
+        int waves;
+    };
+    std::vector<Rows> rows;
     bool generic = false, any_adapt = false, nt = false;
     int blocks = 0;  // persistent aggregation workgroups
 };
@@ -282,16 +252,26 @@ int batch_build(const BatchParams& bp, const Plan* plans, uint8_t* const* ws_bas
     std::vector<WorkItem>& work = B.work;
     std::vector<std::array<WorkItem, kQuad>> quads;
     std::vector<WorkItem> singles;  // items without an opposite partner
-    size_t census_blocks = 0, cost_blocks = 0, wta_blocks = 0, post_blocks = 0;
+    size_t census_blocks = 0, cost_blocks = 0, post_blocks = 0;
     std::vector<BatchItem>& desc = B.desc;
     desc.assign(n, BatchItem{});
     work.clear();
     const bool generic = !(bp.cw == 9 && bp.ch == 7);
-    size_t cost_smem = 0, wta_smem = 0, post_smem = 0;
+    size_t cost_smem = 0, post_smem = 0;
     bool any_adapt = false;
-    for (int i = 0; i < n; ++i) {
+    // the pairs in the order of their row-kernel variants
+    auto variant = [&](int i) {
         const Plan& p = plans[i];
-        const Workspace ws = workspace_carve(p, ws_base[i]);
+        return std::array<int, 5>{p.Dp, p.n_paths, p.l16, 2 * p.pmax <= 255, p.subpixel};
+    };
+    std::vector<int> order(n);
+    for (int i = 0; i < n; ++i) order[i] = i;
+    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return variant(a) < variant(b); });
+    B.rows.clear();
+    for (int i = 0; i < n; ++i) {
+        const int src = order[i];
+        const Plan& p = plans[src];
+        const Workspace ws = workspace_carve(p, ws_base[src]);
         int gh, gv;
         default_lanes(p, &gh, &gv);
         // the batch kernel has 32- and 16-lane groups; the runner's tuning,
@@ -299,9 +279,9 @@ int batch_build(const BatchParams& bp, const Plan* plans, uint8_t* const* ws_bas
         gh = bp.lanes_h ? bp.lanes_h : (gh == 32 ? 32 : 16);
         gv = bp.lanes_v ? bp.lanes_v : 16;
         BatchItem& d = desc[i];
-        d.left = items[i].left;
-        d.right = items[i].right;
-        d.out = items[i].out;
+        d.left = items[src].left;
+        d.right = items[src].right;
+        d.out = items[src].out;
         d.census_l = ws.census_l;
         d.census_r = ws.census_r;
         d.cost = ws.cost;
@@ -332,16 +312,19 @@ int batch_build(const BatchParams& bp, const Plan* plans, uint8_t* const* ws_bas
                                  : (size_t)2 * ((p.W + kCenTX - 1) / kCenTX) * ((p.H + kCenTY - 1) / kCenTY);
         d.cost_blk0 = (int)cost_blocks;
         cost_blocks += (size_t)nsgm * ((p.W + kCostTX - 1) / kCostTX) * p.H;
-        d.wta_blk0 = (int)wta_blocks;
-        wta_blocks += (size_t)nsgm * p.H;
+        if (i == 0 || variant(src) != variant(order[i - 1]))
+            B.rows.push_back({p.Dp, i, 0, RowVariant{p.n_paths, p.l16, false, 2 * p.pmax <= 255, p.subpixel}, 0, 0, 1});
+        BatchLaunch::Rows& rw = B.rows.back();
+        rw.n += 1;
+        d.wta_blk0 = (int)rw.blocks;
+        rw.blocks += (size_t)nsgm * p.H;
+        rw.smem = std::max(rw.smem, row_smem_bytes(p.W, p.lrcheck && !p.lr_full));
+        rw.waves = std::max(rw.waves, row_waves(p.W, p.Dp, p.l16));
         d.post_blk0 = (int)post_blocks;
         if (p.median || p.lrcheck) post_blocks += p.H;
         const int nright = kCostTX + p.D - 1;
         cost_smem = std::max(cost_smem, 8 * (size_t)((kCostTX + nright + 1) & ~1) + (size_t)kCostTX * (p.Dp + 16));
-        if (p.lrcheck) {
-            wta_smem = std::max(wta_smem, 4 * (size_t)(p.W + kWtaGuard));
-            post_smem = std::max(post_smem, 2 * (size_t)p.W);
-        }
+        if (p.lrcheck) post_smem = std::max(post_smem, 2 * (size_t)p.W);
         for (int sg = 0; sg < nsgm; ++sg)
             for (int r = 0; r < p.n_paths; ++r) {
                 const Dir dir = direction(p.n_paths, r);
@@ -420,10 +403,8 @@ int batch_build(const BatchParams& bp, const Plan* plans, uint8_t* const* ws_bas
     B.any_adapt = any_adapt;
     B.census_blocks = census_blocks;
     B.cost_blocks = cost_blocks;
-    B.wta_blocks = wta_blocks;
     B.post_blocks = post_blocks;
     B.cost_smem = cost_smem;
-    B.wta_smem = wta_smem;
     B.post_smem = post_smem;
     return SGM_OK;
 }
@@ -438,8 +419,17 @@ hipError_t batch_launch(const BatchParams& bp, const BatchLaunch& B, const Batch
     const int nquads = (int)(B.work.size() / kQuad);
     (B.any_adapt ? launch_batch_agg_adapt : launch_batch_agg)(B.nt, B.blocks, d_items, d_work, nquads, counter, bp.P1,
                                                               bp.P2, s);
-    hipLaunchKernelGGL(B.nt ? wta_batch_kernel<true> : wta_batch_kernel<false>, dim3((unsigned)B.wta_blocks),
-                       dim3(1024), B.wta_smem, s, d_items, n);
+    for (const BatchLaunch::Rows& r : B.rows) {
+        RowLaunch a{};
+        a.items = d_items + r.first;
+        a.n = r.n;
+        a.P1 = bp.P1;
+        a.P2 = bp.P2;
+        RowVariant v = r.v;
+        v.nt = B.nt;
+        auto launch = r.Dp == 64 ? launch_row_64 : (r.Dp == 128 ? launch_row_128 : launch_row_256);
+        if (hipError_t e = launch(a, v, (int)r.blocks, r.waves, r.smem, s)) return e;
+    }
     if (B.post_blocks > 0) {
         // pairs without a post stage own empty block ranges; the search for
         // the last pair whose range starts at or before a block skips them

@@ -22,7 +22,8 @@ struct BatchItem {
     uint16_t* dl;
     uint16_t* dr;
     int W, H, D, Dp, P, cmax, l16, median, lrcheck, thr, csct, gh, gv, subpixel, lr_full, adaptive;
-    int census_blk0, cost_blk0, wta_blk0, post_blk0;  // first block in each launch
+    int census_blk0, cost_blk0, wta_blk0, post_blk0;  // first block in each launch (wta_blk0: in
+                                                      // the row launch of its kernel variant)
 };
 
 // One aggregation work item: S = 64 / G slices of one direction of one pair;
@@ -39,6 +40,20 @@ struct WorkItem {
 // pixel's costs then run on one CU and its L2, and the second read can hit
 // there, as in the single-pair aggregation launch.
 constexpr int kQuad = 4;
+
+// Index of the pair whose block range [blk0, next blk0) holds block b.
+template <int BatchItem::*FIRST>
+__device__ inline int find_item(const BatchItem* items, int n, int b) {
+    int lo = 0, hi = n;  // items[lo].*FIRST <= b < items[hi].*FIRST
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (items[mid].*FIRST <= b)
+            lo = mid;
+        else
+            hi = mid;
+    }
+    return lo;
+}
 
 void launch_batch_agg(bool nt, int blocks, const BatchItem* items, const WorkItem* work, int nquads,
                       unsigned* queue_counter, int P1, int P2, hipStream_t stream);

@@ -18,9 +18,9 @@ __device__ __attribute__((always_inline)) inline void aggregate_item(const Slice
                                                                      int lane) {
     if (kind == kHoriz) {
         if (g == 32)
-            aggregate_wave<32, Dp / 32, LT, kHoriz, false, ADAPT, NT>(s, first, lane);
+            aggregate_wave<32, Dp / 32, LT, kHoriz, false, ADAPT, NT, CkptSink>(s, first, lane);
         else
-            aggregate_wave<16, Dp / 16, LT, kHoriz, false, ADAPT, NT>(s, first, lane);
+            aggregate_wave<16, Dp / 16, LT, kHoriz, false, ADAPT, NT, CkptSink>(s, first, lane);
     } else if (kind == kVert) {
         if (g == 32)
             aggregate_wave<32, Dp / 32, LT, kVert, false, ADAPT, NT>(s, first, lane);

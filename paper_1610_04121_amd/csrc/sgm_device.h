@@ -22,6 +22,10 @@ namespace dev {
 
 
 
+// The byte the cost volume holds at padded levels d >= D.  The aggregation
+// on byte planes reads it as the high byte of 0x03FF (unpack_selector).
+constexpr uint32_t kPadCost = 3;
+
 __device__ inline int clampi(int v, int lo, int hi) { return v < lo ? lo : (v > hi ? hi : v); }
 
 // 16-byte store at byte offset `ofs` of [base, base + bytes) through a
@@ -336,7 +340,7 @@ __device__ inline void cost_block(const CostArgs& a, int bx, int y, uint64_t* cw
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     const int d = d0 + 4 * q + j;
-                    uint32_t c = 0;  // padded levels d >= D
+                    uint32_t c = kPadCost;  // padded levels d >= D
                     if (d < D) {
                         const uint32_t pc = (uint32_t)__popcll(base ^ word(4 * q + j));
                         const bool out = RB ? x + d >= a.W : x - d < 0;
@@ -516,7 +520,7 @@ __device__ inline void census_cost_block(const CensusCostArgs& a, int bx, int y,
 #pragma unroll
                     for (int j = 0; j < 4; ++j) {
                         const int d = d0 + 4 * q + j;
-                        uint32_t c = 0;  // padded levels d >= D
+                        uint32_t c = kPadCost;  // padded levels d >= D
                         if (d < D) {
                             const uint32_t pc = (uint32_t)__popcll(base ^ m[15 - (4 * q + j)]);
                             c = x - d < 0 ? (uint32_t)a.cmax : pc;
@@ -713,10 +717,11 @@ __device__ inline void unpack_costs(const typename Raw<CPL>::T& r, const uint32_
 }
 
 // Selector of pair k for a lane whose first disparity is d0: low half b_k,
-// high half b_{k+CPL/2} (bytes of the v_perm source pair), and the padding
-// value `pad` (a 16-bit v_perm selector) for d >= D.
+// high half b_{k+CPL/2} (bytes of the v_perm source pair); for d >= D
+// 0x03FF (the level's own byte kPadCost above 0xFF) with `byte_planes`, else
+// 0xFFFF.
 template <int CPL>
-__device__ inline uint32_t unpack_selector(int k, int d0, int D, uint32_t pad) {
+__device__ inline uint32_t unpack_selector(int k, int d0, int D, bool byte_planes) {
     constexpr int NP = CPL / 2;
     uint32_t lo, hi;
     if constexpr (CPL == 2) {
@@ -729,8 +734,8 @@ __device__ inline uint32_t unpack_selector(int k, int d0, int D, uint32_t pad) {
         lo = k % 4;
         hi = 4 + k % 4;
     }
-    const uint32_t slo = (d0 + k < D) ? (lo | 0x0C00u) : pad;
-    const uint32_t shi = (d0 + k + NP < D) ? (hi | 0x0C00u) : pad;
+    const uint32_t slo = (d0 + k < D) ? (lo | 0x0C00u) : (byte_planes ? (lo << 8) | 0x0Du : 0x0D0Du);
+    const uint32_t shi = (d0 + k + NP < D) ? (hi | 0x0C00u) : (byte_planes ? (hi << 8) | 0x0Du : 0x0D0Du);
     return slo | (shi << 16);
 }
 
@@ -900,18 +905,31 @@ __device__ inline uint32_t pack_selector(int k, int d0, int D, uint32_t pad) {
 template <int CPL> struct Prefetch { static constexpr int N = CPL >= 16 ? 8 : 16; };
 template <int CPL> struct FusedPrefetch { static constexpr int N = CPL >= 16 ? 2 : 4; };
 
-// Where aggregate_wave puts each step's L values: by default the direction's
-// L_r plane in global memory.  A sink (the final pass's LDS ring) instead
-// receives put(step, L) for every step and chunk_done() after every Prefetch
-// steps and after the last step.
+// Where aggregate_wave puts each step's values E = L - C in [0, P2]: by
+// default the direction's plane in global memory; with CkptSink only every
+// kRowSegment-th column of it (horizontal directions: the states the row
+// kernel starts from).  A sink (the final pass's LDS ring) instead receives
+// put(step, E) for every step and chunk_done() after every Prefetch steps and
+// after the last step.  (The census-computing variant stores L.)
 struct PlaneSink {};
+struct CkptSink {};
+
+// Columns per segment of the row kernel, which runs both horizontal
+// directions again inside every segment: a horizontal direction keeps its
+// values only where it enters a segment.
+template <int Dp, typename LT>
+struct RowSegment {
+    static constexpr int N = sizeof(LT) == 2 ? 8 : 16;
+};
 
 // ADAPT: the P2 of each step adapts to the base image's intensity change
 // along the path (adaptive_p2); the intensities are prefetched with the costs.
 template <int G, int CPL, typename LT, int KIND, bool FUSED, bool ADAPT = false, bool NT = false,
           typename SINK = PlaneSink>
 __device__ inline void aggregate_wave(const SliceArgs& a, int first_slice, int lane, SINK* sink = nullptr) {
-    constexpr bool kToPlane = std::is_same_v<SINK, PlaneSink>;
+    constexpr bool kCkpt = std::is_same_v<SINK, CkptSink>;
+    constexpr bool kToPlane = std::is_same_v<SINK, PlaneSink> || kCkpt;
+    static_assert(!kCkpt || (KIND == kHoriz && !FUSED), "checkpoints are for horizontal directions");
     static_assert(!(FUSED && ADAPT), "adaptive P2 uses the cost-volume variant");
     constexpr int NP = CPL / 2;
     constexpr int Dp = G * CPL;
@@ -923,28 +941,32 @@ __device__ inline void aggregate_wave(const SliceArgs& a, int first_slice, int l
     const int W = a.W, H = a.H;
     const int grp = lane / G, q = lane % G;
     const int nslices = KIND == kHoriz ? H : W;
-    const int steps = KIND == kHoriz ? W : H;
+    // Checkpoints: left-to-right walks end with the last column before a
+    // segment, right-to-left ones with the first column of segment 1
+    constexpr int SEG = RowSegment<G * CPL, LT>::N;
+    const int steps = kCkpt ? (rx > 0 ? (W - 1) / SEG * SEG : W - SEG) : (KIND == kHoriz ? W : H);
+    if (kCkpt && steps <= 0) return;
     // groups past the last slice repeat the last slice (identical stores)
     const int jg = min(grp, nslices - 1 - first_slice);
 
-    // Byte planes (Cmax + largest step penalty <= 255) keep every register
-    // value far below 0x7C00, so the minimum of three runs as one packed f16
-    // minimum (vmin3h).  That needs finite stand-ins for "no candidate":
-    //   * padded levels d >= D get cost 255 (not 0xFFFF).  Their L stays in
-    //     [255, 255 + P2] and never undercuts a real level: real L <= Cmax +
-    //     P2 <= 255, and the path minimum m is at most Cmax, so m + P2 <=
-    //     255 <= L(pad) + P1.
+    // Byte planes (largest step penalty <= 255) keep every register value far
+    // below 0x7C00, so the minimum of three runs as one packed f16 minimum
+    // (vmin3h).  That needs finite stand-ins for "no candidate":
+    //   * padded levels d >= D get cost 1023.  Their L stays in [1023, 1278]
+    //     and never undercuts a real level: the path minimum m is at most
+    //     Cmax <= 64, so m + P2 <= 319 < L(pad) + P1.  (The census-computing
+    //     variant, whose planes hold L <= Cmax + P2 <= 255, uses 255.)
     //   * the d - 1 / d + 1 candidate beyond the lane group's ends is 0x0FFF
     //     (OR-ed into a value below 0x1000), above every real candidate.
     //   * P1 is capped at the largest step penalty: a larger P1 never wins
     //     against m + P2 in Eq. 3 (L(d +- 1) >= m), and neither does the cap.
     // 16-bit planes keep saturating u16 arithmetic with 0xFFFF.
     constexpr bool kF16 = sizeof(LT) == 1;
-    const uint32_t pad = kF16 ? 0x0C0Du : 0x0D0Du;  // v_perm bytes: 0x00FF or 0xFFFF
     uint32_t sel[NP];
 #pragma unroll
     for (int k = 0; k < NP; ++k)
-        sel[k] = FUSED ? pack_selector<CPL>(k, q * CPL, a.D, pad) : unpack_selector<CPL>(k, q * CPL, a.D, pad);
+        sel[k] = FUSED ? pack_selector<CPL>(k, q * CPL, a.D, kF16 ? 0x0C0Du : 0x0D0Du)  // 0x00FF or 0xFFFF
+                       : unpack_selector<CPL>(k, q * CPL, a.D, kF16);
     const uint32_t inf = kF16 ? 0x0FFFu : 0xFFFFu;
     const uint32_t edge_lo = q == 0 ? inf << 16 : 0u;  // no d-1 below d = 0
     const uint32_t edge_hi = q == G - 1 ? inf : 0u;    // no d+1 above Dp-1
@@ -972,13 +994,18 @@ __device__ inline void aggregate_wave(const SliceArgs& a, int first_slice, int l
     };
     const int pstep = KIND == kHoriz ? rx : ry * W + (KIND == kDiag ? rx : 0);
     Pos cur;
-    cur.t = 0;
+    // a right-to-left walk with checkpoints starts so that its blocks end at
+    // multiples of PF and SEG: its first steps (t < 0) repeat the first column
+    // and the path starts after them
+    constexpr int kAlign = PF > SEG ? PF : SEG;
+    const int t_first = kCkpt && rx < 0 ? -((kAlign - W % kAlign) % kAlign) : 0;
+    cur.t = t_first;
     cur.x = KIND == kHoriz ? (rx > 0 ? 0 : W - 1) : first_slice;
     cur.pix = KIND == kHoriz ? first_slice * W + cur.x : (ry > 0 ? 0 : H - 1) * W + cur.x;
     // a position stays on the slice's last step, so the lookahead never
     // leaves the slice
     auto advance = [&](Pos& p) {
-        const bool more = p.t + 1 < steps;
+        const bool more = p.t + 1 < steps && (!kCkpt || p.t >= 0);
         p.t += 1;
         p.pix += more ? pstep : 0;
         if constexpr (KIND == kHoriz) p.x += more ? rx : 0;
@@ -1015,7 +1042,7 @@ __device__ inline void aggregate_wave(const SliceArgs& a, int first_slice, int l
     if constexpr (ADAPT && KIND == kDiag) ax = first_slice + jg + rx * (lane & (PF - 1));
     auto adapt_load = [&](int t0) {  // intensities of steps t0 + (lane mod PF) and the one before
         if constexpr (ADAPT) {
-            const int t = min(t0 + (lane & (PF - 1)), steps - 1);
+            const int t = max(min(t0 + (lane & (PF - 1)), steps - 1), 0);
 #pragma unroll
             for (int b = 0; b < 2; ++b) {
                 const int u = max(t - b, 0);
@@ -1093,6 +1120,7 @@ __device__ inline void aggregate_wave(const SliceArgs& a, int first_slice, int l
     // reduction: the barrier to the compiler's scheduler at the end of a step
     // keeps them there (without it the unpacks of many steps were gathered
     // at the top of a block, where they waited for loads just issued).
+    // `store` gets E = L - C (L for the census-computing variant).
     auto step = [&](const RawT& next, const Pos& pn, int j, auto&& store) {
         auto fence = [] { __builtin_amdgcn_sched_barrier(0); };
         u16x2 p2v = P2v;
@@ -1100,15 +1128,15 @@ __device__ inline void aggregate_wave(const SliceArgs& a, int first_slice, int l
             p2v = as2(row_broadcast(p2blk, j));
             fence();
         }
-        u16x2 L[NP];
+        u16x2 L[NP], E[NP];
 #pragma unroll
-        for (int k = 0; k < NP; ++k) L[k] = R[k] - mm;
+        for (int k = 0; k < NP; ++k) E[k] = R[k] - mm;
         fence();
 #pragma unroll
-        for (int k = 0; k < NP; ++k) L[k] = vmin(L[k], p2v);
+        for (int k = 0; k < NP; ++k) E[k] = vmin(E[k], p2v);
         fence();
 #pragma unroll
-        for (int k = 0; k < NP; ++k) L[k] = kF16 ? L[k] + c[k] : vadds(L[k], c[k]);
+        for (int k = 0; k < NP; ++k) L[k] = kF16 ? E[k] + c[k] : vadds(E[k], c[k]);
         fence();
         // minimum over the lane's cells, replicated in both halves
         u16x2 tm;
@@ -1154,7 +1182,7 @@ __device__ inline void aggregate_wave(const SliceArgs& a, int first_slice, int l
                 lo0 = as2(__builtin_amdgcn_alignbit(as1(lp[NP - 1]), prev, 16));
                 hiN = as2(__builtin_amdgcn_alignbit(nxt, as1(lp[0]), 16));
             } else if constexpr (I == 2) {
-                store(L);
+                store(FUSED ? L : E);
             } else {
 #pragma unroll
                 for (int k = 0; k < NP; ++k) {
@@ -1167,6 +1195,12 @@ __device__ inline void aggregate_wave(const SliceArgs& a, int first_slice, int l
         };
         mm = as2(group_min<G>(as1(tm), fill));
     };
+    int k = t_first;  // step of the block's slot 0
+    // whether slot j of the block is a column the row kernel starts from
+    auto at_checkpoint = [&](int j) -> bool {
+        if constexpr (PF >= SEG) return (j + 1) % SEG == 0;
+        return (j + 1) % PF == 0 && (k - t_first + PF) % SEG == 0;
+    };
     // a step at `cur` in the general form (restarts, wraps, any position)
     auto step_at_cur = [&](const RawT& next, int j) {
         if constexpr (KIND == kDiag) {
@@ -1177,9 +1211,19 @@ __device__ inline void aggregate_wave(const SliceArgs& a, int first_slice, int l
                 mm = as2(0u);
             }
         }
+        if constexpr (kCkpt) {
+            if (cur.t == 0) {
+#pragma unroll
+                for (int k = 0; k < NP; ++k) R[k] = as2(0u);
+                mm = as2(0u);
+            }
+        }
         const Pos here = cur;
         advance(cur);
         step(next, cur, j, [&](const u16x2 (&L)[NP]) {
+            if constexpr (kCkpt) {
+                if (!at_checkpoint(j) || here.t < 0) return;
+            }
             if constexpr (kToPlane)
                 store_l<CPL, LT, NT>(rl, (uint32_t)((here.pix + lane_px(here)) * Dp + qofs) * (uint32_t)sizeof(LT), 0u, L);
             else
@@ -1187,7 +1231,7 @@ __device__ inline void aggregate_wave(const SliceArgs& a, int first_slice, int l
         });
     };
 
-    adapt_load(0);
+    adapt_load(cur.t);
     adapt_lookup();
     Pos ahead = cur;
     // Dropped stores (an empty buffer) between the first loads, so that a
@@ -1199,7 +1243,7 @@ __device__ inline void aggregate_wave(const SliceArgs& a, int first_slice, int l
     for (int j = 0; j < PF; ++j) {
         ring[j] = load_at(ahead);
         __builtin_amdgcn_sched_barrier(0);
-        if constexpr (kToPlane) buffer_store<0>(rnone, 0u, 0u, 0u);
+        if constexpr (kToPlane && !kCkpt) buffer_store<0>(rnone, 0u, 0u, 0u);
         __builtin_amdgcn_sched_barrier(0);
         advance(ahead);
     }
@@ -1207,7 +1251,6 @@ __device__ inline void aggregate_wave(const SliceArgs& a, int first_slice, int l
 
     // Up to PF steps with the loads of the PF steps after them, in the general
     // form: any position, the slice's end, restarts and wraps.
-    int k = 0;
     auto chunk_any = [&](auto whole) {
         p2blk = p2next;
         adapt_load(k + PF);
@@ -1251,6 +1294,7 @@ __device__ inline void aggregate_wave(const SliceArgs& a, int first_slice, int l
                 if (j == kLookupStep) adapt_lookup();
                 ring[j] = buffer_load_raw<CPL>(rc, vo, so);
                 step(ring[(j + 1) % PF], cur, j, [&](const u16x2 (&L)[NP]) {
+                    if (kCkpt && !at_checkpoint(j)) return;
                     if constexpr (kToPlane)
                         store_l<CPL, LT, NT>(rls, vo * (uint32_t)sizeof(LT), so * (uint32_t)sizeof(LT), L);
                     else
@@ -1286,6 +1330,7 @@ __device__ inline void aggregate_wave(const SliceArgs& a, int first_slice, int l
             chunk_any(std::true_type{});
         }
     } else if constexpr (!FUSED) {
+        while (kCkpt && k < 0 && k + PF <= steps) chunk_any(std::true_type{});
         while (k + 2 * PF <= steps) chunk_fast();
     }
     while (k < steps) chunk_any(std::false_type{});
@@ -1319,6 +1364,9 @@ struct WtaArgs {
     uint16_t* dr;  // right disparity or nullptr
     int W, H, D, Dp, nplanes;
     int subpixel = 0;  // dl in 1/16 pixel: parabola vertex through S(d-1), S(d), S(d+1)
+    // planes of E = L - C: the cost volume, counted once per path; nullptr
+    // when the planes hold L
+    const uint8_t* cost = nullptr;
     // The post stage run inside the WTA launch (rowcnt != nullptr): per-row
     // counters (zeroed by the census launch of the same frame), `contrib`
     // blocks writing raw rows per image row (2 when one launch makes D_L and
@@ -1335,6 +1383,20 @@ __device__ inline int floor_div(int num, int den) {
 }
 
 constexpr int kWtaGuard = 256;  // >= max disparity
+
+// Left disparity in 1/16 pixel: the vertex of the parabola through va =
+// S(d - 1), S(d) and vc = S(d + 1) at the winner's key best = (S(d) << 8) | d,
+// rounded half up: f = floor((16 (a - c) + den) / (2 den)), den = a + c - 2b
+__device__ inline uint32_t subpixel_q4(uint32_t best, uint32_t va, uint32_t vc, int D) {
+    const int d = (int)(best & 0xFF);
+    int f = 0;
+    if (d > 0 && d < D - 1) {
+        const int b = (int)((best >> 8) & 0xFFFFu);
+        const int den = (int)va + (int)vc - 2 * b;
+        if (den > 0) f = floor_div(16 * ((int)va - (int)vc) + den, 2 * den);
+    }
+    return (uint32_t)(16 * d + f);
+}
 
 // Sums of 16 disparities d0..d0+15 of one pixel over NPL planes as 8 packed
 // pairs; pair k holds disparities dpair(k) (see below).  Every plane's load
@@ -1385,6 +1447,19 @@ __device__ inline void sum16(const LT* base, size_t plane, uint32_t (&S)[8]) {
 #pragma unroll
             for (int k = 0; k < 8; ++k) S[k] = as1(as2(S[k]) + as2(w[k]));
         }
+    }
+}
+
+// Adds n times the 16 cost bytes at p to the pairs S of sum16<LT>.
+template <typename LT>
+__device__ inline void add_costs16(const uint8_t* p, int n, uint32_t (&S)[8]) {
+    const uint4 q = load16<false>(p);
+    const uint32_t w[4] = {q.x, q.y, q.z, q.w};
+    const u16x2 nn = as2((uint32_t)n * 0x10001u);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        const uint32_t sel = sizeof(LT) == 1 ? ((k & 1) ? 0x0C030C01u : 0x0C020C00u) : ((k & 1) ? 0x0C030C02u : 0x0C010C00u);
+        S[k] = as1(as2(S[k]) + as2(__builtin_amdgcn_perm(0u, w[k >> 1], sel)) * nn);
     }
 }
 
@@ -1451,9 +1526,7 @@ __device__ inline void wta_cells(const WtaArgs& a, int y, int x, int g, int G, c
     const int dbest = (int)(best & 0xFF);
     uint32_t outv = (uint32_t)dbest;
     if (a.subpixel) {
-        // S(dbest - 1) and S(dbest + 1) from the lanes holding them; the
-        // vertex of the parabola through the three, rounded half up to
-        // 1/16: f = floor((16 (a - c) + den) / (2 den)), den = a + c - 2b
+        // S(dbest - 1) and S(dbest + 1) from the lanes holding them
         uint32_t va = ~0u, vc = ~0u;
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
@@ -1465,15 +1538,7 @@ __device__ inline void wta_cells(const WtaArgs& a, int y, int x, int g, int G, c
             if (d0 + dlo == dbest + 1) vc = slo;
             if (d0 + dhi == dbest + 1) vc = shi;
         }
-        va = lanes_min(va, G);
-        vc = lanes_min(vc, G);
-        int f = 0;
-        if (dbest > 0 && dbest < a.D - 1) {
-            const int b = (int)((best >> 8) & 0xFFFFu);
-            const int den = (int)va + (int)vc - 2 * b;
-            if (den > 0) f = floor_div(16 * ((int)va - (int)vc) + den, 2 * den);
-        }
-        outv = (uint32_t)(16 * dbest + f);
+        outv = subpixel_q4(best, lanes_min(va, G), lanes_min(vc, G), a.D);
     }
     if (g == 0 && valid) a.dl[(size_t)y * a.W + x] = (uint16_t)outv;
 }
@@ -1495,7 +1560,9 @@ __device__ inline void wta_row_impl(const WtaArgs& a, int y, uint32_t* keyR_smem
     for (int i = threadIdx.x; i < a.W * G; i += blockDim.x) {
         const int x = i >> gshift, g = i & (G - 1);
         uint32_t S[8];
-        sum16<LT, NPL, NT>(planes + ((size_t)y * a.W + x) * a.Dp + 16 * g, a.plane, S);
+        const size_t at = ((size_t)y * a.W + x) * a.Dp + 16 * g;
+        sum16<LT, NPL, NT>(planes + at, a.plane, S);
+        if (a.cost) add_costs16<LT>(a.cost + at, NPL, S);
         wta_cells<LT>(a, y, x, g, G, S, keyR, right);
     }
     if (right) {
@@ -1552,7 +1619,7 @@ __device__ inline void wta_row(const WtaArgs& a, int y, uint32_t* keyR_smem) {
 // ---------------------------------------------------------------------------
 struct FinalArgs {
     SliceArgs agg;          // the fused direction: cost volume, rx = +-1, ry = 0
-    const uint8_t* planes;  // the other P - 1 directions' u8 planes, contiguous
+    const uint8_t* planes;  // the other P - 1 directions' u8 planes (E = L - C), contiguous
     size_t plane;           // bytes per plane (W * H * Dp)
     WtaArgs wta;            // outputs D_L (dl) and D_R (dr, or nullptr), W, H, D, Dp
     uint16_t* s_out;        // debug: S u16 [H][W][D], or nullptr
@@ -1590,7 +1657,7 @@ struct FinalAhead {
     static constexpr int N = n < 1 ? 1 : (n > 3 ? 3 : n);
 };
 
-// A producer's sink: step t's L values of row slot `row` go to
+// A producer's sink: step t's values E of row slot `row` go to
 // ring[(t / K) % 2][t % K][row][Dp] as bytes in disparity order.
 template <int Dp>
 struct LdsRingSink {
@@ -1647,9 +1714,10 @@ __device__ inline uint32_t final_item_offset(const FinalArgs& f, const FinalItem
 
 // One item of a chunk: every lane runs it (invalid items only skip the
 // stores and key updates inside wta_cells).
+// q: the bytes of the NPL stored planes and, last, of the cost volume
 template <int Dp, int NPL>
 __device__ inline void final_item_finish(const FinalArgs& f, const FinalItem<Dp>& it, int buf, const uint8_t* ring,
-                                         uint32_t* keyR, const uint4 (&q)[NPL]) {
+                                         uint32_t* keyR, const uint4 (&q)[NPL + 1]) {
     using L = FinalLayout<Dp>;
     uint32_t S[8];
 #pragma unroll
@@ -1664,6 +1732,15 @@ __device__ inline void final_item_finish(const FinalArgs& f, const FinalItem<Dp>
     };
 #pragma unroll
     for (int p = 0; p < NPL; ++p) add(q[p]);
+    {
+        const uint32_t w[4] = {q[NPL].x, q[NPL].y, q[NPL].z, q[NPL].w};
+        const u16x2 nn = as2((uint32_t)(NPL + 1) * 0x10001u);  // every path's L = E + C
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            S[2 * k] = as1(as2(S[2 * k]) + as2(__builtin_amdgcn_perm(0u, w[k], 0x0C020C00u)) * nn);
+            S[2 * k + 1] = as1(as2(S[2 * k + 1]) + as2(__builtin_amdgcn_perm(0u, w[k], 0x0C030C01u)) * nn);
+        }
+    }
     add(*reinterpret_cast<const uint4*>(ring + ((buf * L::K + it.j) * L::R + it.row) * Dp + 16 * it.g));
     const int W = f.wta.W;
     wta_cells<uint8_t>(f.wta, it.y, it.x, it.g, Dp / 16, S, keyR + it.row * (W + kWtaGuard) + kWtaGuard,
@@ -1693,23 +1770,24 @@ __device__ inline void final_pass_block(const FinalArgs& f, int blk, uint8_t* sm
     } else {
         const int ctid = (wave - L::NPROD) * 64 + lane;
         const int nchunks = (W + L::K - 1) / L::K;
-        __amdgpu_buffer_rsrc_t rp[NPL];
+        __amdgpu_buffer_rsrc_t rp[NPL + 1];
 #pragma unroll
         for (int p = 0; p < NPL; ++p) rp[p] = buffer_rsrc(f.planes + f.plane * p, (uint32_t)f.plane);
-        constexpr int A = FinalAhead<L::M, NPL>::N;
+        rp[NPL] = buffer_rsrc(f.agg.cost, (uint32_t)f.plane);
+        constexpr int A = FinalAhead<L::M, NPL + 1>::N;
         // plane bytes of the lane's M items of chunks c .. c + A - 1, slot c % A
-        uint4 q[A][L::M][NPL];
+        uint4 q[A][L::M][NPL + 1];
         auto item = [&](int c, int m) { return FinalItem<Dp>(f, y0, c, ctid + m * 64 * L::NC); };
 #pragma unroll
         for (int s = 0; s < A; ++s)
 #pragma unroll
-            for (int m = 0; m < L::M; ++m) load_planes16<NPL, NT>(rp, final_item_offset<Dp>(f, item(s, m)), q[s][m]);
-        auto chunk = [&](int c, uint4 (&qs)[L::M][NPL]) {
+            for (int m = 0; m < L::M; ++m) load_planes16<NPL + 1, NT>(rp, final_item_offset<Dp>(f, item(s, m)), q[s][m]);
+        auto chunk = [&](int c, uint4 (&qs)[L::M][NPL + 1]) {
             __syncthreads();  // chunk c is in the ring
 #pragma unroll
             for (int m = 0; m < L::M; ++m) final_item_finish<Dp, NPL>(f, item(c, m), c & 1, ring, keyR, qs[m]);
 #pragma unroll
-            for (int m = 0; m < L::M; ++m) load_planes16<NPL, NT>(rp, final_item_offset<Dp>(f, item(c + A, m)), qs[m]);
+            for (int m = 0; m < L::M; ++m) load_planes16<NPL + 1, NT>(rp, final_item_offset<Dp>(f, item(c + A, m)), qs[m]);
         };
         int c0 = 0;
         for (; c0 + A <= nchunks; c0 += A) {

@@ -9,6 +9,7 @@
 #include "sgm_agg.h"
 #include "sgm_device.h"
 #include "sgm_plan.h"
+#include "sgm_row.h"
 
 namespace sgm {
 
@@ -65,28 +66,29 @@ __global__ __launch_bounds__(256) void post_kernel(PostArgs a) {
     post_row(a, blockIdx.x, post_smem);
 }
 
-// Debug tap: S = sum of planes, u16 [H][W][D].
-// Plane `skip` (-1: none) is left out.
+// Debug tap: S = sum of L_r over planes (of L_r - C; of L_r without cost),
+// u16 [H][W][D].  Plane `skip` (-1: none) is left out.
 template <typename LT>
-__global__ void sum_planes_kernel(const void* lbuf, size_t plane, uint16_t* s, int W, int H, int D,
+__global__ void sum_planes_kernel(const void* lbuf, const uint8_t* cost, size_t plane, uint16_t* s, int W, int H, int D,
                                   int Dp, int nplanes, int skip) {
     const size_t n = (size_t)W * H * D;
     for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
         const size_t p = i / D, d = i - p * D;
         uint32_t acc = 0;
         for (int k = 0; k < nplanes; ++k)
-            if (k != skip) acc += reinterpret_cast<const LT*>(lbuf)[plane * k + p * Dp + d];
+            if (k != skip) acc += reinterpret_cast<const LT*>(lbuf)[plane * k + p * Dp + d] + (cost ? cost[p * Dp + d] : 0);
         s[i] = (uint16_t)acc;
     }
 }
 
-// Debug tap: one L_r plane (or the cost volume) as u16 [H][W][D].
+// Debug tap: one L_r (a plane of L_r - C and the costs, or a plane of L_r or
+// the cost volume alone) as u16 [H][W][D].
 template <typename LT>
-__global__ void extract_plane_kernel(const LT* src, uint16_t* out, int W, int H, int D, int Dp) {
+__global__ void extract_plane_kernel(const LT* src, const uint8_t* cost, uint16_t* out, int W, int H, int D, int Dp) {
     const size_t n = (size_t)W * H * D;
     for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
         const size_t p = i / D, d = i - p * D;
-        out[i] = (uint16_t)src[p * Dp + d];
+        out[i] = (uint16_t)(src[p * Dp + d] + (cost ? cost[p * Dp + d] : 0));
     }
 }
 
@@ -119,9 +121,12 @@ bool plan_finish(Plan& p, const char** why) {
                                : "n_paths * (Cmax + P2) must be <= 65535 (16-bit summed costs)");
     if (p.lr_thr < 0) return fail("lr threshold must be >= 0");
     p.Dp = padded_disp(p.D);
-    p.l16 = p.cmax + pmax > 255;
-    // Normal stores leave a frame's L_r planes in the 256 MiB memory-side
-    // cache for the WTA to read back.  When the planes and the cost volume
+    p.pmax = (int)pmax;
+    // the planes hold L_r - C in [0, pmax] (from the last term of Eq. 3)
+    p.l16 = pmax > 255;
+    p.wide = p.cmax + pmax > 255;
+    // Normal stores leave a frame's planes in the 256 MiB memory-side cache
+    // for the row kernel (or WTA) to read back.  When the planes and the cost volume
     // do not fit, the dirty planes would be written back while the WTA reads,
     // so they are stored non-temporally instead.
     {
@@ -142,7 +147,7 @@ size_t workspace_bytes(const Plan& p) {
     const size_t npx = (size_t)p.W * p.H;
     const size_t cells = npx * p.Dp;
     const int nsgm = p.lr_full ? 2 : 1;
-    return align256(cells) + align256(cells * nsgm * p.n_paths * (p.l16 ? 2 : 1)) + 2 * align256(npx * 2) +
+    return align256(cells) + align256(cells * nsgm * p.n_paths * (p.l16 || p.wide ? 2 : 1)) + 2 * align256(npx * 2) +
            2 * align256(8 * (npx + kCensusGuard)) + align256(4 * (size_t)p.H) + (p.lr_full ? align256(cells) : 0);
 }
 
@@ -154,7 +159,7 @@ Workspace workspace_carve(const Plan& p, void* base) {
     ws.cost = b;
     b += align256(cells);
     ws.lbuf = b;
-    b += align256(cells * (p.lr_full ? 2 : 1) * p.n_paths * (p.l16 ? 2 : 1));
+    b += align256(cells * (p.lr_full ? 2 : 1) * p.n_paths * (p.l16 || p.wide ? 2 : 1));
     ws.dl = reinterpret_cast<uint16_t*>(b);
     b += align256(npx * 2);
     ws.dr = reinterpret_cast<uint16_t*>(b);
@@ -277,10 +282,11 @@ void default_lanes(const Plan& p, int* gh, int* gv) {
     *gv = 16;
 }
 
-bool fused_aggregation(const Plan& p) { return p.fused && !p.lr_full && !p.adaptive; }
+// (it stores L_r itself, which byte planes hold up to Cmax + pmax = 255)
+bool fused_aggregation(const Plan& p) { return p.fused && !p.lr_full && !p.adaptive && (p.l16 || !p.wide); }
 
 hipError_t launch_aggregate(const Plan& p, const Workspace& ws, hipStream_t stream, const uint8_t* left,
-                            const uint8_t* right, bool skip_last) {
+                            const uint8_t* right, bool skip_last, bool checkpoints) {
     int gh = p.lanes_h, gv = p.lanes_v;
     if (gh <= 0 || gv <= 0) default_lanes(p, &gh, &gv);
     if (p.Dp == 64) {  // 64 lanes need at least 2 levels per lane
@@ -290,6 +296,7 @@ hipError_t launch_aggregate(const Plan& p, const Workspace& ws, hipStream_t stre
     if (p.adaptive && (!left || (p.lr_full && !right))) return hipErrorInvalidValue;
     AggArgs a;
     fill_agg_args(p, ws, left, right, 64 / gh, 64 / gv, a, skip_last);
+    a.ckpt = checkpoints ? 1 : 0;
     // the store policy is an instruction operand: a second instantiation of
     // the plain (stored-cost, constant-P2) kernels
     const AggVariant v{gh, gv, p.l16, fused_aggregation(p), p.adaptive, p.nt_store && !p.adaptive && !fused_aggregation(p)};
@@ -343,11 +350,17 @@ bool post_folded(const Plan& p) { return p.post_in_wta && (p.median || p.lrcheck
 
 hipError_t launch_aggregate_wta(const Plan& p, const Workspace& ws, const uint8_t* left, const uint8_t* right,
                                 uint16_t* out, hipStream_t stream, hipEvent_t mid_event, bool post_in_wta) {
-    const bool fp = final_pass_active(p);
-    hipError_t e = launch_aggregate(p, ws, stream, left, right, fp);
+    const bool fp = final_pass_active(p), row = row_kernel_active(p, post_in_wta);
+    hipError_t e = launch_aggregate(p, ws, stream, left, right, fp, row);
     if (e == hipSuccess && mid_event) e = hipEventRecord(mid_event, stream);
-    if (e == hipSuccess) e = fp ? launch_final_pass(p, ws, out, stream) : launch_wta(p, ws, out, stream, post_in_wta);
+    if (e == hipSuccess)
+        e = fp ? launch_final_pass(p, ws, out, stream)
+               : (row ? launch_row(p, ws, left, right, out, stream) : launch_wta(p, ws, out, stream, post_in_wta));
     return e;
+}
+
+bool row_kernel_active(const Plan& p, bool post_in_wta) {
+    return !final_pass_active(p) && !fused_aggregation(p) && !post_in_wta;
 }
 
 // Whether the L_r planes were stored non-temporally, so the WTA streams them
@@ -359,16 +372,39 @@ static PostArgs post_args(const Plan& p, const Workspace& ws, uint16_t* out) {
     return PostArgs{ws.dl, ws.dr, out, p.W, p.H, p.median ? 1 : 0, p.lrcheck ? 1 : 0, p.lr_thr, p.subpixel ? 1 : 0};
 }
 
+hipError_t launch_row(const Plan& p, const Workspace& ws, const uint8_t* left, const uint8_t* right, uint16_t* out,
+                      hipStream_t stream) {
+    const bool post = p.median || p.lrcheck;
+    const size_t plane = (size_t)p.W * p.H * p.Dp;
+    RowLaunch a{};
+    a.l = RowArgs{ws.cost, ws.lbuf, left, post ? ws.dl : out, p.lrcheck && !p.lr_full ? ws.dr : nullptr,
+                  p.W, p.H, p.D, p.P1, p.P2, p.n_paths, p.adaptive ? 1 : 0, p.subpixel ? 1 : 0};
+    if (p.lr_full) {  // the right-base SGM's winners are D_R
+        a.r = a.l;
+        a.r.cost = ws.cost_r;
+        a.r.planes = static_cast<const uint8_t*>(ws.lbuf) + plane * p.n_paths * (p.l16 ? 2 : 1);
+        a.r.img = right;
+        a.r.dl = ws.dr;
+        a.r.subpixel = 0;
+    }
+    const RowVariant v{p.n_paths, p.l16, planes_nt(p), 2 * p.pmax <= 255, p.subpixel};
+    const int blocks = p.lr_full ? 2 * p.H : p.H;
+    const size_t smem = row_smem_bytes(p.W, a.l.dr != nullptr);
+    auto launch = p.Dp == 64 ? launch_row_64 : (p.Dp == 128 ? launch_row_128 : launch_row_256);
+    return launch(a, v, blocks, row_waves(p.W, p.Dp, p.l16), smem, stream);
+}
+
 hipError_t launch_wta(const Plan& p, const Workspace& ws, uint16_t* out, hipStream_t stream, bool post_in_wta) {
     const bool nt = planes_nt(p);
     const bool post = p.median || p.lrcheck;
     const bool fold = post_in_wta && post;
+    const uint8_t* cost = fused_aggregation(p) ? nullptr : ws.cost;  // planes of L - C need C
     if (fold && !ws.rowcnt) return hipErrorInvalidValue;
     if (p.lr_full) {
         const size_t plane = (size_t)p.W * p.H * p.Dp;
         const void* rbuf = static_cast<const uint8_t*>(ws.lbuf) + plane * p.n_paths * (p.l16 ? 2 : 1);
-        WtaArgs l{ws.lbuf, plane, ws.dl, nullptr, p.W, p.H, p.D, p.Dp, p.n_paths, p.subpixel ? 1 : 0};
-        WtaArgs r{rbuf, plane, ws.dr, nullptr, p.W, p.H, p.D, p.Dp, p.n_paths};
+        WtaArgs l{ws.lbuf, plane, ws.dl, nullptr, p.W, p.H, p.D, p.Dp, p.n_paths, p.subpixel ? 1 : 0, cost};
+        WtaArgs r{rbuf, plane, ws.dr, nullptr, p.W, p.H, p.D, p.Dp, p.n_paths, 0, ws.cost_r};
         size_t smem = 0;
         if (fold) {  // D_L and D_R rows come from separate blocks
             for (WtaArgs* w : {&l, &r}) {
@@ -386,7 +422,7 @@ hipError_t launch_wta(const Plan& p, const Workspace& ws, uint16_t* out, hipStre
         return hipGetLastError();
     }
     WtaArgs a{ws.lbuf, (size_t)p.W * p.H * p.Dp, post ? ws.dl : out, p.lrcheck ? ws.dr : nullptr,
-              p.W, p.H, p.D, p.Dp, p.n_paths, p.subpixel ? 1 : 0};
+              p.W, p.H, p.D, p.Dp, p.n_paths, p.subpixel ? 1 : 0, cost};
     if (fold) {
         a.rowcnt = ws.rowcnt;
         a.post = post_args(p, ws, out);
@@ -436,11 +472,12 @@ hipError_t launch_sum_planes(const Plan& p, const Workspace& ws, uint16_t* s_out
                              int nplanes) {
     const size_t plane = (size_t)p.W * p.H * p.Dp;
     if (nplanes < 0) nplanes = p.n_paths;
+    const uint8_t* cost = fused_aggregation(p) ? nullptr : ws.cost;
     if (p.l16)
-        hipLaunchKernelGGL(sum_planes_kernel<uint16_t>, dim3(1024), dim3(256), 0, stream, ws.lbuf, plane, s_out,
+        hipLaunchKernelGGL(sum_planes_kernel<uint16_t>, dim3(1024), dim3(256), 0, stream, ws.lbuf, cost, plane, s_out,
                            p.W, p.H, p.D, p.Dp, nplanes, skip);
     else
-        hipLaunchKernelGGL(sum_planes_kernel<uint8_t>, dim3(1024), dim3(256), 0, stream, ws.lbuf, plane, s_out,
+        hipLaunchKernelGGL(sum_planes_kernel<uint8_t>, dim3(1024), dim3(256), 0, stream, ws.lbuf, cost, plane, s_out,
                            p.W, p.H, p.D, p.Dp, nplanes, skip);
     return hipGetLastError();
 }
@@ -448,15 +485,17 @@ hipError_t launch_sum_planes(const Plan& p, const Workspace& ws, uint16_t* s_out
 hipError_t launch_extract_plane(const Plan& p, const Workspace& ws, int plane, uint16_t* out,
                                 hipStream_t stream) {
     const size_t cells = (size_t)p.W * p.H * p.Dp;
+    const uint8_t* cost = fused_aggregation(p) ? nullptr : (plane < p.n_paths ? ws.cost : ws.cost_r);
+    const uint8_t* none = nullptr;
     if (plane < 0)  // -1: the cost volume, -2: the right-base cost volume
         hipLaunchKernelGGL(extract_plane_kernel<uint8_t>, dim3(1024), dim3(256), 0, stream,
-                           plane == -2 ? ws.cost_r : ws.cost, out, p.W, p.H, p.D, p.Dp);
+                           plane == -2 ? ws.cost_r : ws.cost, none, out, p.W, p.H, p.D, p.Dp);
     else if (p.l16)
         hipLaunchKernelGGL(extract_plane_kernel<uint16_t>, dim3(1024), dim3(256), 0, stream,
-                           reinterpret_cast<const uint16_t*>(ws.lbuf) + cells * plane, out, p.W, p.H, p.D, p.Dp);
+                           reinterpret_cast<const uint16_t*>(ws.lbuf) + cells * plane, cost, out, p.W, p.H, p.D, p.Dp);
     else
         hipLaunchKernelGGL(extract_plane_kernel<uint8_t>, dim3(1024), dim3(256), 0, stream,
-                           reinterpret_cast<const uint8_t*>(ws.lbuf) + cells * plane, out, p.W, p.H, p.D, p.Dp);
+                           reinterpret_cast<const uint8_t*>(ws.lbuf) + cells * plane, cost, out, p.W, p.H, p.D, p.Dp);
     return hipGetLastError();
 }
 

@@ -24,8 +24,11 @@ struct Plan {
     bool adaptive = false;     // P2 of each step from the base image's intensity change
     int lr_thr = 1;
     int cmax = 0;              // largest matching cost
-    bool l16 = false;          // L_r stored as u16 (else u8: Cmax + P2 <= 255)
-    bool nt_store = false;     // L_r stores non-temporal: the planes and cost
+    int pmax = 0;              // largest penalty of one step: L_r - C is in [0, pmax]
+    bool l16 = false;          // planes stored as u16 (else u8: pmax <= 255)
+    bool wide = false;         // Cmax + pmax > 255: the workspace holds u16 planes
+                               // (its size does not depend on l16)
+    bool nt_store = false;     // plane stores non-temporal: the planes and cost
                                // volume of a frame exceed the memory-side cache
     bool fused = false;        // aggregation computes costs from census words
                                // instead of reading the cost volume
@@ -41,8 +44,9 @@ struct Plan {
 // Device workspace of one pair.  All buffers are row-major, d fastest.
 struct Workspace {
     uint8_t* cost = nullptr;   // C   u8 [H][W][Dp]
-    void* lbuf = nullptr;      // L_r u8|u16 [n_paths][H][W][Dp]; with lr_full the
-                               // right-base planes follow: [2 * n_paths][H][W][Dp]
+    void* lbuf = nullptr;      // planes of L_r - C u8|u16 [n_paths][H][W][Dp] (of L_r
+                               // with the census-computing aggregation); with lr_full
+                               // the right-base planes follow: [2 * n_paths][H][W][Dp]
     uint8_t* cost_r = nullptr; // right-base C_R u8 [H][W][Dp] (lr_full only)
     uint16_t* dl = nullptr;    // raw left disparity  u16 [H][W]
     uint16_t* dr = nullptr;    // raw right disparity u16 [H][W]
@@ -95,8 +99,19 @@ bool census_cost_fusable(const Plan& p);
 // left / right: the caller's images (the base images of the adaptive P2).
 // skip_last: every direction but last_direction(p), whose L_r the final
 // pass computes; the other planes are then numbered 0 .. n_paths - 2.
+// checkpoints: the horizontal directions store only the columns the row
+// kernel needs.
 hipError_t launch_aggregate(const Plan& p, const Workspace& ws, hipStream_t stream, const uint8_t* left = nullptr,
-                            const uint8_t* right = nullptr, bool skip_last = false);
+                            const uint8_t* right = nullptr, bool skip_last = false, bool checkpoints = false);
+// Whether the row kernel follows the aggregation (the horizontal directions
+// then store checkpoints): every plan but those whose tuning asks for the
+// final pass, the post stage inside the WTA launch or the census-computing
+// aggregation.
+bool row_kernel_active(const Plan& p, bool post_in_wta);
+// The row kernel: sum and winner-take-all with the horizontal directions run
+// again inside; raw maps, or `out` when no post stage follows.
+hipError_t launch_row(const Plan& p, const Workspace& ws, const uint8_t* left, const uint8_t* right, uint16_t* out,
+                      hipStream_t stream);
 // Whether the final pass replaces the last direction's aggregation and the
 // WTA launch: the tuning asks for it and the plan allows it (u8 planes, the
 // cost volume, no full check, no adaptive P2, its LDS fits).
