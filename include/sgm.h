@@ -121,7 +121,8 @@ int sgm_compute(sgm_ctx *ctx, const uint8_t *left, const uint8_t *right, uint16_
  *   lanes_h - lanes per horizontal aggregation slice (16, 32 or 64), lanes_v
  *   - lanes per vertical / diagonal slice (16 or 32), with lanes_h >= lanes_v
  *   (the shapes 16/16, 32/16, 32/32, 64/16 and 64/32; 64 acts as 32 when the
- *   padded range is 64 levels); 0 and 0 select the built-in default.
+ *   padded range is 64 levels); 0 and 0 select the built-in default, which
+ *   depends on the image size, range and path count.
  *   fused   - bit SGM_TUNE_FUSED_AGG: the aggregation computes the matching
  *   costs from census words itself (no cost volume in memory); otherwise a
  *   cost kernel writes the u8 cost volume C[H][W][Dp] that the aggregation
@@ -214,8 +215,8 @@ int sgm_batch_compute(sgm_batch *b, const sgm_item *items, int n, sgm_stream_t s
 
 /* Kernel shape of the batched aggregation (results never depend on it):
  * lanes per horizontal slice (16 or 32) and per other slice (16 or 32) for
- * every pair; 0 keeps the per-pair default (32 horizontal lanes when the
- * image is wider than tall, else 16; 16 for the other directions). */
+ * every pair; 0 keeps the default (16; 32 horizontal lanes for ranges above
+ * 64 in a batch too small to fill the device). */
 int sgm_batch_set_tuning(sgm_batch *b, int lanes_h, int lanes_v);
 
 /* Workgroups (4 wavefronts each) of the persistent aggregation grid: 0, the

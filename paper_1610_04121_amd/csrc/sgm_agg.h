@@ -27,11 +27,11 @@ struct AggArgs {
     // the horizontal directions keep only the columns the row kernel enters
     // its segments from (CkptSink)
     int ckpt;
+    int gh, gv;  // lanes per horizontal (16, 32, 64) / other (16, 32) slice
 };
 
 // Which instantiation of the aggregation kernel to launch.
 struct AggVariant {
-    int gh, gv;  // lanes per horizontal / other slice
     bool l16, fused, adaptive, nt;
 };
 

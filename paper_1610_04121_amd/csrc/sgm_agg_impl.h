@@ -11,9 +11,9 @@ namespace {
 using namespace dev;
 
 // One launch covers every direction.  Horizontal slices (the longest when
-// W > H) may use a different group width GH than the others (GV), so that
-// the longest dependency chains get the fewest instructions per step.
-template <int GH, int GV, int Dp, typename LT, bool FUSED, bool ADAPT, bool NT>
+// W > H) may use a different group width than the others, so that the longest
+// dependency chains get the fewest instructions per step.
+template <int Dp, typename LT, bool FUSED, bool ADAPT, bool NT>
 __global__ __launch_bounds__(256) void aggregate_kernel(AggArgs a) {
     __shared__ uint16_t p2lut[ADAPT ? 256 : 1];
     if constexpr (ADAPT) {  // every wave of the block takes part before any leaves
@@ -52,49 +52,57 @@ __global__ __launch_bounds__(256) void aggregate_kernel(AggArgs a) {
     s.img = a.img[r];
     s.p2lut = ADAPT ? p2lut : nullptr;
     s.lplane = reinterpret_cast<LT*>(a.lbuf) + (size_t)s.plane * a.plane_index[r];
-    if (s.ry == 0) {
-        if constexpr (!FUSED) {
+    auto walk = [&](auto lanes, auto kind) {
+        constexpr int G = decltype(lanes)::value, KIND = decltype(kind)::value;
+        const int first = local * (64 / G);
+        if constexpr (KIND == kHoriz && !FUSED) {
             if (a.ckpt) {
-                aggregate_wave<GH, Dp / GH, LT, kHoriz, FUSED, ADAPT, NT, CkptSink>(s, local * (64 / GH), lane);
+                aggregate_wave<G, Dp / G, LT, KIND, FUSED, ADAPT, NT, CkptSink>(s, first, lane);
                 return;
             }
         }
-        aggregate_wave<GH, Dp / GH, LT, kHoriz, FUSED, ADAPT, NT>(s, local * (64 / GH), lane);
+        aggregate_wave<G, Dp / G, LT, KIND, FUSED, ADAPT, NT>(s, first, lane);
+    };
+    using std::integral_constant;
+    if (s.ry == 0) {
+        const integral_constant<int, kHoriz> kind;
+        if constexpr (Dp >= 128) {  // 64 lanes need at least 2 levels per lane
+            if (a.gh == 64) {
+                walk(integral_constant<int, 64>{}, kind);
+                return;
+            }
+        }
+        if (a.gh == 32)
+            walk(integral_constant<int, 32>{}, kind);
+        else
+            walk(integral_constant<int, 16>{}, kind);
     } else if (s.rx == 0) {
-        aggregate_wave<GV, Dp / GV, LT, kVert, FUSED, ADAPT, NT>(s, local * (64 / GV), lane);
+        const integral_constant<int, kVert> kind;
+        if (a.gv == 32)
+            walk(integral_constant<int, 32>{}, kind);
+        else
+            walk(integral_constant<int, 16>{}, kind);
     } else {
-        aggregate_wave<GV, Dp / GV, LT, kDiag, FUSED, ADAPT, NT>(s, local * (64 / GV), lane);
+        const integral_constant<int, kDiag> kind;
+        if (a.gv == 32)
+            walk(integral_constant<int, 32>{}, kind);
+        else
+            walk(integral_constant<int, 16>{}, kind);
     }
-}
-
-template <int GH, int GV, int Dp, typename LT, bool FUSED, bool ADAPT, bool NT>
-hipError_t launch_agg_t(const AggArgs& a, hipStream_t stream) {
-    hipLaunchKernelGGL((aggregate_kernel<GH, GV, Dp, LT, FUSED, ADAPT, NT>), dim3((a.total + 3) / 4), dim3(256), 0,
-                       stream, a);
-    return hipGetLastError();
 }
 
 template <int Dp, typename LT, bool FUSED, bool ADAPT, bool NT>
-hipError_t launch_agg_lanes(const AggArgs& a, const AggVariant& v, hipStream_t stream) {
-    switch (v.gh * 100 + v.gv) {
-        case 1616: return launch_agg_t<16, 16, Dp, LT, FUSED, ADAPT, NT>(a, stream);
-        case 3216: return launch_agg_t<32, 16, Dp, LT, FUSED, ADAPT, NT>(a, stream);
-        case 3232: return launch_agg_t<32, 32, Dp, LT, FUSED, ADAPT, NT>(a, stream);
-        default: break;
-    }
-    if constexpr (Dp >= 128) {  // 64 lanes need at least 2 levels per lane
-        if (v.gh == 64 && v.gv == 16) return launch_agg_t<64, 16, Dp, LT, FUSED, ADAPT, NT>(a, stream);
-        if (v.gh == 64 && v.gv == 32) return launch_agg_t<64, 32, Dp, LT, FUSED, ADAPT, NT>(a, stream);
-    }
-    return hipErrorInvalidValue;
+hipError_t launch_agg_t(const AggArgs& a, hipStream_t stream) {
+    hipLaunchKernelGGL((aggregate_kernel<Dp, LT, FUSED, ADAPT, NT>), dim3((a.total + 3) / 4), dim3(256), 0, stream, a);
+    return hipGetLastError();
 }
 
 template <int Dp, typename LT>
 hipError_t launch_agg_lt(const AggArgs& a, const AggVariant& v, hipStream_t stream) {
-    if (v.adaptive) return launch_agg_lanes<Dp, LT, false, true, false>(a, v, stream);
-    if (v.fused) return launch_agg_lanes<Dp, LT, true, false, false>(a, v, stream);
-    if (v.nt) return launch_agg_lanes<Dp, LT, false, false, true>(a, v, stream);
-    return launch_agg_lanes<Dp, LT, false, false, false>(a, v, stream);
+    if (v.adaptive) return launch_agg_t<Dp, LT, false, true, false>(a, stream);
+    if (v.fused) return launch_agg_t<Dp, LT, true, false, false>(a, stream);
+    if (v.nt) return launch_agg_t<Dp, LT, false, false, true>(a, stream);
+    return launch_agg_t<Dp, LT, false, false, false>(a, stream);
 }
 
 template <int Dp>

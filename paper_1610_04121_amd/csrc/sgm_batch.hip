@@ -268,16 +268,22 @@ int batch_build(const BatchParams& bp, const Plan* plans, uint8_t* const* ws_bas
     for (int i = 0; i < n; ++i) order[i] = i;
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return variant(a) < variant(b); });
     B.rows.clear();
+    long long waves16 = 0;  // wavefronts of the aggregation at 16 lanes a slice
+    for (int i = 0; i < n; ++i)
+        for (int r = 0; r < plans[i].n_paths; ++r)
+            waves16 += (plans[i].lr_full ? 2 : 1) * ((slice_count(plans[i].W, plans[i].H, direction(plans[i].n_paths, r)) + 3) / 4);
     for (int i = 0; i < n; ++i) {
         const int src = order[i];
         const Plan& p = plans[src];
         const Workspace ws = workspace_carve(p, ws_base[src]);
-        int gh, gv;
-        default_lanes(p, &gh, &gv);
         // the batch kernel has 32- and 16-lane groups; the runner's tuning,
-        // when set, applies to every pair
-        gh = bp.lanes_h ? bp.lanes_h : (gh == 32 ? 32 : 16);
-        gv = bp.lanes_v ? bp.lanes_v : 16;
+        // when set, applies to every pair.  By default 16 lanes, which take
+        // the fewest instructions per cell, unless the whole batch is too
+        // small to give each SIMD a wavefront and its steps' length counts
+        // (64 mixed pairs: 16/16 7229 us, 32/16 7438; 8 small pairs, D <= 64:
+        // 109 and 114).
+        const int gh = bp.lanes_h ? bp.lanes_h : (p.Dp > 64 && waves16 <= 1024 ? 32 : 16);
+        const int gv = bp.lanes_v ? bp.lanes_v : 16;
         BatchItem& d = desc[i];
         d.left = items[src].left;
         d.right = items[src].right;

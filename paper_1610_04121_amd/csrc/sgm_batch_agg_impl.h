@@ -56,8 +56,11 @@ __global__ __launch_bounds__(256) void aggregate_batch_kernel(const BatchItem* i
                                                               int nquads, unsigned* queue_counter, int P1, int P2) {
     __shared__ uint16_t p2lut[ANY_ADAPT ? 256 : 1];
     __shared__ unsigned quad;
-    if constexpr (ANY_ADAPT)  // P1, P2 belong to the batch: one table per block
+    __shared__ uint16_t p2const[ANY_ADAPT ? 256 : 1];
+    if constexpr (ANY_ADAPT) {  // P1, P2 belong to the batch: one table per block
         fill_p2_lut(p2lut, P1, P2);
+        p2const[threadIdx.x] = (uint16_t)P2;
+    }
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     for (;;) {
@@ -82,17 +85,19 @@ __global__ __launch_bounds__(256) void aggregate_batch_kernel(const BatchItem* i
         s.p2lut = ANY_ADAPT ? p2lut : nullptr;
         const int kind = w.ry == 0 ? kHoriz : (w.rx == 0 ? kVert : kDiag);
         const int g = kind == kHoriz ? it.gh : it.gv;
-        if (ANY_ADAPT && it.adaptive) {
-            if (it.l16)
-                aggregate_item_dp<uint16_t, NT, ANY_ADAPT>(s, it.Dp, kind, g, w.first, lane);
-            else
-                aggregate_item_dp<uint8_t, NT, ANY_ADAPT>(s, it.Dp, kind, g, w.first, lane);
-        } else {
-            if (it.l16)
-                aggregate_item_dp<uint16_t, NT, false>(s, it.Dp, kind, g, w.first, lane);
-            else
-                aggregate_item_dp<uint8_t, NT, false>(s, it.Dp, kind, g, w.first, lane);
+        // in a batch with an adaptive-P2 pair the others take the same code
+        // with a table of their constant P2 (and, as without it, P1 capped at
+        // the largest penalty of a step on byte planes)
+        if constexpr (ANY_ADAPT) {
+            if (!it.adaptive) {
+                s.p2lut = p2const;
+                if (!it.l16) s.P1 = min(P1, P2);
+            }
         }
+        if (it.l16)
+            aggregate_item_dp<uint16_t, NT, ANY_ADAPT>(s, it.Dp, kind, g, w.first, lane);
+        else
+            aggregate_item_dp<uint8_t, NT, ANY_ADAPT>(s, it.Dp, kind, g, w.first, lane);
     }
 }
 

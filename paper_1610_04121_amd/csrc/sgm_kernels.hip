@@ -275,11 +275,50 @@ static void fill_agg_args(const Plan& p, const Workspace& ws, const uint8_t* lef
     }
 }
 
-// Group widths: horizontal slices are the longest chains on wide images,
-// so they get more lanes (fewer instructions per step); the rest use 16.
+// Group widths (lanes per slice).  More lanes make a step shorter and the
+// wavefronts more.  With at most one wavefront per SIMD (1024) the longest
+// chain sets the time, so the widest shape that fits one round wins; beyond
+// that, what counts is how full the last round is.  Whole calls (us), median +
+// check: 451x377, D = 128, 8 paths: 16/16 (865 wavefronts) 98, 32/16 (1054)
+// 110; 451x377, D = 128, 4 paths: 32/32 (828) 69.5, 32/16 75.3; 640x480, D =
+// 128, 4 paths: 32/16 (800) 95, 32/32 (1120) 108; 640x480, D = 256, 2 paths:
+// 64/32 (800) 112, 32/16 135; 640x480, D = 128, 8 paths: 64/16 (1920, 0.94 of
+// two rounds) 155, 32/16 (1440, 0.70) 161; 800x600, D = 128, 8 paths: 32/32
+// (3000, 0.98) 255, 32/16 (1800, 0.88) 272; 1242x375, D = 128, 8 paths: 64/16
+// (2613, 0.85) 248, 32/16 (2238, 0.73) 262.  With 64 levels a 16-lane step is
+// as short as a 32-lane one (320x240: 43.2 and 45.0), except with many
+// directions over several rounds (1242x375, 8 paths: 32/16 151, 16/16 159).
+// 64 horizontal lanes beyond one round only pay with diagonals (640x480 4
+// paths: 115).  Two SGMs (the full check) are not narrowed to fit one round
+// (1242x375, 4 paths: 16/16 239, 32/16 223).
 void default_lanes(const Plan& p, int* gh, int* gv) {
-    *gh = p.W > p.H ? 32 : 16;
-    *gv = 16;
+    constexpr int kSimds = 1024;
+    const int nsgm = p.lr_full ? 2 : 1;
+    const int horiz = p.n_paths == 2 ? 1 : 2, other = p.n_paths - horiz;
+    auto waves = [&](int h, int v) {
+        const int sh = 64 / h, sv = 64 / v;
+        return nsgm * (horiz * ((p.H + sh - 1) / sh) + other * ((p.W + sv - 1) / sv));
+    };
+    auto set = [&](int h, int v) {
+        *gh = h;
+        *gv = v;
+    };
+    if (p.Dp == 64) {
+        const bool many = waves(16, 16) > kSimds && nsgm * p.n_paths >= 8;
+        return many ? set(32, 16) : set(16, 16);
+    }
+    if (p.Dp == 256 && waves(64, 32) <= kSimds) return set(64, 32);
+    if (waves(32, 32) <= kSimds) return set(32, 32);
+    if (waves(32, 16) <= kSimds) return set(32, 16);
+    if (waves(16, 16) <= kSimds && nsgm == 1) return set(16, 16);
+    auto fill = [&](int h, int v) {  // share of the rounds' SIMDs in use
+        const int w = waves(h, v);
+        return (double)w / (kSimds * (double)((w + kSimds - 1) / kSimds));
+    };
+    set(32, 16);
+    const int shapes[3][2] = {{16, 16}, {32, 32}, {64, 16}};
+    for (const auto& sh : shapes)
+        if ((sh[0] < 64 || p.n_paths == 8) && fill(sh[0], sh[1]) > 1.05 * fill(*gh, *gv)) set(sh[0], sh[1]);
 }
 
 // (it stores L_r itself, which byte planes hold up to Cmax + pmax = 255)
@@ -289,17 +328,16 @@ hipError_t launch_aggregate(const Plan& p, const Workspace& ws, hipStream_t stre
                             const uint8_t* right, bool skip_last, bool checkpoints) {
     int gh = p.lanes_h, gv = p.lanes_v;
     if (gh <= 0 || gv <= 0) default_lanes(p, &gh, &gv);
-    if (p.Dp == 64) {  // 64 lanes need at least 2 levels per lane
-        gh = std::min(gh, 32);
-        gv = std::min(gv, 32);
-    }
+    if (p.Dp == 64) gh = std::min(gh, 32);  // 64 lanes need at least 2 levels per lane
     if (p.adaptive && (!left || (p.lr_full && !right))) return hipErrorInvalidValue;
     AggArgs a;
     fill_agg_args(p, ws, left, right, 64 / gh, 64 / gv, a, skip_last);
     a.ckpt = checkpoints ? 1 : 0;
+    a.gh = gh;
+    a.gv = gv;
     // the store policy is an instruction operand: a second instantiation of
     // the plain (stored-cost, constant-P2) kernels
-    const AggVariant v{gh, gv, p.l16, fused_aggregation(p), p.adaptive, p.nt_store && !p.adaptive && !fused_aggregation(p)};
+    const AggVariant v{p.l16, fused_aggregation(p), p.adaptive, p.nt_store && !p.adaptive && !fused_aggregation(p)};
     if (p.Dp == 64) return launch_agg_64(a, v, stream);
     if (p.Dp == 128) return launch_agg_128(a, v, stream);
     return launch_agg_256(a, v, stream);
@@ -359,8 +397,18 @@ hipError_t launch_aggregate_wta(const Plan& p, const Workspace& ws, const uint8_
     return e;
 }
 
+// The row kernel trades two plane passes for running the horizontal
+// directions twice, so it pays where the planes' bytes set the time.  The
+// whole call with plain WTA against row kernel (us, one frame): 320x240 D = 64
+// 4 paths (19.7 M cell-paths) 44.6 / 44.4, 320x240 D = 128 8 paths (79 M) 59.8 /
+// 60.7, 451x377 D = 128 2 paths (44 M) 68.2 / 69.8, 640x480 D = 64 4 paths
+// (79 M) 79.3 / 76.7, 640x480 D = 128 4 paths (157 M) 99.8 / 94.8, 1280x720
+// D = 128 8 paths (944 M) 491 / 421; 96x64 D = 64 4 paths (1.6 M) 24.0 / 25.6.
+constexpr long long kRowKernelCells = 72ll << 20;
+
 bool row_kernel_active(const Plan& p, bool post_in_wta) {
-    return !final_pass_active(p) && !fused_aggregation(p) && !post_in_wta;
+    return (long long)p.W * p.H * p.Dp * p.n_paths > kRowKernelCells && !final_pass_active(p) && !fused_aggregation(p) &&
+           !post_in_wta;
 }
 
 // Whether the L_r planes were stored non-temporally, so the WTA streams them

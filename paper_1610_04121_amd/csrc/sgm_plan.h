@@ -104,9 +104,9 @@ bool census_cost_fusable(const Plan& p);
 hipError_t launch_aggregate(const Plan& p, const Workspace& ws, hipStream_t stream, const uint8_t* left = nullptr,
                             const uint8_t* right = nullptr, bool skip_last = false, bool checkpoints = false);
 // Whether the row kernel follows the aggregation (the horizontal directions
-// then store checkpoints): every plan but those whose tuning asks for the
-// final pass, the post stage inside the WTA launch or the census-computing
-// aggregation.
+// then store checkpoints): frames above a size, unless the tuning asks for
+// the final pass, the post stage inside the WTA launch or the
+// census-computing aggregation.
 bool row_kernel_active(const Plan& p, bool post_in_wta);
 // The row kernel: sum and winner-take-all with the horizontal directions run
 // again inside; raw maps, or `out` when no post stage follows.

@@ -33,12 +33,13 @@ hipError_t launch_row_128(const RowLaunch& a, const RowVariant& v, int blocks, i
 hipError_t launch_row_256(const RowLaunch& a, const RowVariant& v, int blocks, int waves, size_t smem, hipStream_t stream);
 
 // Wavefronts of a row's workgroup: a wavefront takes 4 segments at a time (2
-// with 256 levels), in as few rounds of at most 8 wavefronts as there are,
-// evenly.
+// with 256 levels).  8 wavefronts put two on each SIMD of a CU; 5 or 7 leave
+// SIMDs unequally loaded (1242x375, D = 128, 8 paths, whole call: 275, 265 and
+// 260 us with 5, 7 and 8).
 inline int row_waves(int W, int Dp, bool l16) {
     const int cols = (Dp == 256 ? 2 : 4) * (l16 ? 8 : 16);
-    const int units = (W + cols - 1) / cols, rounds = (units + 7) / 8;
-    return (units + rounds - 1) / rounds;
+    const int units = (W + cols - 1) / cols;
+    return units < 8 ? units : 8;
 }
 
 }  // namespace sgm
