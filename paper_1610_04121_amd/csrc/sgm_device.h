@@ -1653,7 +1653,7 @@ __host__ __device__ inline size_t final_smem_bytes(int Dp, int W, bool right) {
 // registers: 4 * M * NPL registers per chunk.
 template <int M, int NPL>
 struct FinalAhead {
-    static constexpr int n = 16 / (M * NPL);
+    static constexpr int n = 14 / (M * NPL);
     static constexpr int N = n < 1 ? 1 : (n > 3 ? 3 : n);
 };
 
