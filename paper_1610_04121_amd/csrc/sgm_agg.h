@@ -17,7 +17,7 @@ struct AggArgs {
     dev::SliceArgs base;          // shared fields; rx, ry, cost, lplane set per direction
     void* lbuf;              // all L_r planes
     int ndirs, total;
-    int start[kMaxLaunchDirs + 1];  // first wave of each direction
+    int start[kMaxLaunchDirs + 1];  // first slice group of each direction
     int rx[kMaxLaunchDirs], ry[kMaxLaunchDirs], plane_index[kMaxLaunchDirs];
     const uint8_t* cost[kMaxLaunchDirs];  // the cost volume each direction reads
     const uint8_t* img[kMaxLaunchDirs];   // its SGM's base image (adaptive P2)
@@ -28,6 +28,9 @@ struct AggArgs {
     // its segments from (CkptSink)
     int ckpt;
     int gh, gv;  // lanes per horizontal (16, 32, 64) / other (16, 32) slice
+    // wavefronts per slice group (1, 2 or 4 segments, dev::Split); start and
+    // total count slice groups
+    int split;
 };
 
 // Which instantiation of the aggregation kernel to launch.

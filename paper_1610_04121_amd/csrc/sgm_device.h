@@ -922,14 +922,62 @@ struct RowSegment {
     static constexpr int N = sizeof(LT) == 2 ? 8 : 16;
 };
 
+// A slice in segments: S wavefronts of one workgroup (S = 1: the whole slice).
+//
+// Segment 0 starts the path; the others start in the middle from an arbitrary
+// state (a path start), so what they store is provisional.  Once every
+// wavefront of the workgroup has walked its segment, each goes on into the
+// next one, from its own end state, and overwrites what is stored there until
+// it meets an equal value vector: equal E at one pixel is equal L there (the
+// costs are the same), and from equal L the recurrence gives equal values, so
+// the rest of that segment stands.  A wavefront that reaches a segment's end
+// without meeting one goes on into the segment after it in the next round,
+// when the other wavefronts' walks there have ended; segment 0's wavefront
+// carries the true values, so after at most S - 1 rounds every segment holds
+// them, whatever the costs.  On matched images the values meet within 10 to 50
+// steps (a path that follows the surface forgets its start as soon as the
+// other levels lie P2 above it); on unrelated images they may not meet at all
+// and the slice takes its full length again.
+//
+// The point is the chain: a slice's dependent steps are divided by almost S.
+struct Split {
+    int seg = 0, S = 1;
+    int* open = nullptr;  // LDS, one int per wavefront of the workgroup
+    int wave = 0;         // of the workgroup's 4
+
+    // One round's end for a wavefront that goes on (all wavefronts of the
+    // workgroup take part in every round).  Its stores have completed before
+    // the others read them.
+    __device__ void next_round() const {
+        __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+        open[wave] = 1;
+        __syncthreads();
+        __syncthreads();
+    }
+    // Rounds of a wavefront that has ended, until all have.
+    __device__ void finish() const {
+        if (S == 1) return;
+        __builtin_amdgcn_s_waitcnt(0x0F70);
+        for (;;) {
+            open[wave] = 0;
+            __syncthreads();
+            const int any = open[0] | open[1] | open[2] | open[3];
+            __syncthreads();
+            if (__builtin_amdgcn_readfirstlane(any) == 0) return;
+        }
+    }
+};
+
 // ADAPT: the P2 of each step adapts to the base image's intensity change
 // along the path (adaptive_p2); the intensities are prefetched with the costs.
 template <int G, int CPL, typename LT, int KIND, bool FUSED, bool ADAPT = false, bool NT = false,
-          typename SINK = PlaneSink>
-__device__ inline void aggregate_wave(const SliceArgs& a, int first_slice, int lane, SINK* sink = nullptr) {
+          typename SINK = PlaneSink, bool SPLIT = false>
+__device__ inline void aggregate_wave(const SliceArgs& a, int first_slice, int lane, SINK* sink = nullptr,
+                                      const Split& split = Split{}) {
     constexpr bool kCkpt = std::is_same_v<SINK, CkptSink>;
     constexpr bool kToPlane = std::is_same_v<SINK, PlaneSink> || kCkpt;
     static_assert(!kCkpt || (KIND == kHoriz && !FUSED), "checkpoints are for horizontal directions");
+    static_assert(!SPLIT || (kToPlane && !FUSED && sizeof(LT) == 1), "segments are for byte planes of L - C");
     static_assert(!(FUSED && ADAPT), "adaptive P2 uses the cost-volume variant");
     constexpr int NP = CPL / 2;
     constexpr int Dp = G * CPL;
@@ -945,7 +993,10 @@ __device__ inline void aggregate_wave(const SliceArgs& a, int first_slice, int l
     // segment, right-to-left ones with the first column of segment 1
     constexpr int SEG = RowSegment<G * CPL, LT>::N;
     const int steps = kCkpt ? (rx > 0 ? (W - 1) / SEG * SEG : W - SEG) : (KIND == kHoriz ? W : H);
-    if (kCkpt && steps <= 0) return;
+    if (kCkpt && steps <= 0) {
+        if constexpr (SPLIT) split.finish();
+        return;
+    }
     // groups past the last slice repeat the last slice (identical stores)
     const int jg = min(grp, nslices - 1 - first_slice);
 
@@ -999,9 +1050,30 @@ __device__ inline void aggregate_wave(const SliceArgs& a, int first_slice, int l
     // and the path starts after them
     constexpr int kAlign = PF > SEG ? PF : SEG;
     const int t_first = kCkpt && rx < 0 ? -((kAlign - W % kAlign) % kAlign) : 0;
-    cur.t = t_first;
-    cur.x = KIND == kHoriz ? (rx > 0 ? 0 : W - 1) : first_slice;
-    cur.pix = KIND == kHoriz ? first_slice * W + cur.x : (ry > 0 ? 0 : H - 1) * W + cur.x;
+    // the wavefront's segment: whole blocks [t_begin, seg_end) of the slice
+    int t_begin = t_first, seg_len = 0, seg_end = steps;
+    if constexpr (SPLIT) {
+        if (split.S > 1) {
+            const int blocks = (steps - t_first + kAlign - 1) / kAlign;
+            seg_len = (blocks + split.S - 1) / split.S * kAlign;
+            t_begin = t_first + split.seg * seg_len;
+            seg_end = t_begin + seg_len;
+            if (t_begin >= steps) {
+                split.finish();
+                return;
+            }
+        }
+    }
+    cur.t = t_begin;
+    const int t_pos = max(t_begin, 0);
+    cur.x = KIND == kHoriz ? (rx > 0 ? t_pos : W - 1 - t_pos) : first_slice;
+    if constexpr (KIND == kDiag) {
+        if (t_pos > 0) {  // a diagonal wraps once every W steps
+            cur.x = (first_slice + rx * t_pos) % W;
+            cur.x += cur.x < 0 ? W : 0;
+        }
+    }
+    cur.pix = KIND == kHoriz ? first_slice * W + cur.x : (ry > 0 ? t_pos : H - 1 - t_pos) * W + cur.x;
     // a position stays on the slice's last step, so the lookahead never
     // leaves the slice
     auto advance = [&](Pos& p) {
@@ -1039,7 +1111,7 @@ __device__ inline void aggregate_wave(const SliceArgs& a, int first_slice, int l
     // and mm are 0 and the P2 of that step does not matter.)
     uint32_t p2blk = 0, p2next = 0, inten[2] = {0, 0};
     int ax = 0;  // diagonal: the column of the lane's step
-    if constexpr (ADAPT && KIND == kDiag) ax = first_slice + jg + rx * (lane & (PF - 1));
+    if constexpr (ADAPT && KIND == kDiag) ax = cur.x + jg + rx * (lane & (PF - 1));
     auto adapt_load = [&](int t0) {  // intensities of steps t0 + (lane mod PF) and the one before
         if constexpr (ADAPT) {
             const int t = max(min(t0 + (lane & (PF - 1)), steps - 1), 0);
@@ -1195,14 +1267,15 @@ __device__ inline void aggregate_wave(const SliceArgs& a, int first_slice, int l
         };
         mm = as2(group_min<G>(as1(tm), fill));
     };
-    int k = t_first;  // step of the block's slot 0
+    int k = t_begin;  // step of the block's slot 0
+    typename Raw<CPL>::T e_last{};  // segments: what the block's last step stored
     // whether slot j of the block is a column the row kernel starts from
     auto at_checkpoint = [&](int j) -> bool {
         if constexpr (PF >= SEG) return (j + 1) % SEG == 0;
         return (j + 1) % PF == 0 && (k - t_first + PF) % SEG == 0;
     };
     // a step at `cur` in the general form (restarts, wraps, any position)
-    auto step_at_cur = [&](const RawT& next, int j) {
+    auto step_at_cur = [&](const RawT& next, int j, auto fix) {
         if constexpr (KIND == kDiag) {
             const int xl = cur.x + jg >= W ? cur.x + jg - W : cur.x + jg;
             if (xl == border) {
@@ -1223,6 +1296,9 @@ __device__ inline void aggregate_wave(const SliceArgs& a, int first_slice, int l
         step(next, cur, j, [&](const u16x2 (&L)[NP]) {
             if constexpr (kCkpt) {
                 if (!at_checkpoint(j) || here.t < 0) return;
+            }
+            if constexpr (decltype(fix)::value) {
+                if (j == PF - 1) e_last = pack_u8<CPL>(L);
             }
             if constexpr (kToPlane)
                 store_l<CPL, LT, NT>(rl, (uint32_t)((here.pix + lane_px(here)) * Dp + qofs) * (uint32_t)sizeof(LT), 0u, L);
@@ -1251,7 +1327,7 @@ __device__ inline void aggregate_wave(const SliceArgs& a, int first_slice, int l
 
     // Up to PF steps with the loads of the PF steps after them, in the general
     // form: any position, the slice's end, restarts and wraps.
-    auto chunk_any = [&](auto whole) {
+    auto chunk_any = [&](auto whole, auto fix) {
         p2blk = p2next;
         adapt_load(k + PF);
 #pragma unroll
@@ -1260,7 +1336,7 @@ __device__ inline void aggregate_wave(const SliceArgs& a, int first_slice, int l
             if (decltype(whole)::value || k + j < steps) {
                 if (j == kLookupStep) adapt_lookup();
                 ring[j] = load_at(ahead);
-                step_at_cur(ring[(j + 1) % PF], j);
+                step_at_cur(ring[(j + 1) % PF], j, fix);
                 advance(ahead);
             }
         }
@@ -1281,7 +1357,7 @@ __device__ inline void aggregate_wave(const SliceArgs& a, int first_slice, int l
 #pragma unroll
     for (int j = 0; j < (KIND == kHoriz ? PF : 1); ++j)
         vstep[j] = voff + (uint32_t)((KIND == kHoriz ? (rx > 0 ? j : PF - 1 - j) : 0) * Dp);
-    auto chunk_fast = [&]() {
+    auto chunk_fast = [&](auto fix) {
         if constexpr (!FUSED) {
             uint32_t so = (uint32_t)((ahead.pix - (KIND == kHoriz && rx < 0 ? PF - 1 : 0)) * Dp);
             const uint32_t sstep = (uint32_t)(pstep * Dp);
@@ -1295,6 +1371,9 @@ __device__ inline void aggregate_wave(const SliceArgs& a, int first_slice, int l
                 ring[j] = buffer_load_raw<CPL>(rc, vo, so);
                 step(ring[(j + 1) % PF], cur, j, [&](const u16x2 (&L)[NP]) {
                     if (kCkpt && !at_checkpoint(j)) return;
+                    if constexpr (decltype(fix)::value) {
+                        if (j == PF - 1) e_last = pack_u8<CPL>(L);
+                    }
                     if constexpr (kToPlane)
                         store_l<CPL, LT, NT>(rls, vo * (uint32_t)sizeof(LT), so * (uint32_t)sizeof(LT), L);
                     else
@@ -1317,23 +1396,96 @@ __device__ inline void aggregate_wave(const SliceArgs& a, int first_slice, int l
             k += PF;
         }
     };
-    // The conditional steps come last: a loop back from them to the others
-    // would make the compiler wait there for loads that may be recent.
-    if constexpr (KIND == kDiag && !FUSED) {
-        constexpr int S = 64 / G;
-        while (k + PF <= steps) {
-            // no group restarts or wraps, neither in a block nor in the steps
-            // it loads: columns 1 .. W - S - 1 for group 0
-            const int inner = rx > 0 ? (cur.x >= 1 ? (W - S - cur.x) / PF - 1 : 0) : (cur.x < W - S ? cur.x / PF - 1 : 0);
-            const int fast = min((steps - k) / PF - 1, inner);
-            for (int i = 0; i < fast; ++i) chunk_fast();
-            chunk_any(std::true_type{});
+    // Whole blocks of [k, end): runs of inner ones, and the ones around a
+    // diagonal's border crossing or before the slice's end in the general form.
+    // With `fixing`, stops after a block whose last step stored what was there.
+    auto blocks_to = [&](int end, auto fix) -> bool {
+        constexpr bool fixing = decltype(fix)::value;
+        bool agreed = false;
+        typename Raw<CPL>::T e_old{};
+        auto before = [&] {
+            if constexpr (fixing) {
+                // position of the block's last step
+                Pos p = cur;
+                if constexpr (KIND == kDiag) {
+                    const int row0 = p.pix - p.x + (PF - 1) * ry * W;
+                    p.x += (PF - 1) * rx;
+                    while (p.x < 0) p.x += W;
+                    while (p.x >= W) p.x -= W;
+                    p.pix = row0 + p.x;
+                } else {
+                    p.pix += (PF - 1) * pstep;
+                }
+                // device scope: past this CU's cache, which may hold the line
+                // from before another wavefront stored it
+                const uint32_t ofs = (uint32_t)((p.pix + lane_px(p)) * Dp + qofs);
+                if constexpr (CPL == 2) {
+                    e_old = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rl, ofs, 0, 16);
+                } else if constexpr (CPL == 4) {
+                    e_old = __builtin_amdgcn_raw_buffer_load_b32(rl, ofs, 0, 16);
+                } else if constexpr (CPL == 8) {
+                    const auto v = __builtin_amdgcn_raw_buffer_load_b64(rl, ofs, 0, 16);
+                    e_old = make_uint2(v[0], v[1]);
+                } else {
+                    const auto v = __builtin_amdgcn_raw_buffer_load_b128(rl, ofs, 0, 16);
+                    e_old = make_uint4(v[0], v[1], v[2], v[3]);
+                }
+            }
+        };
+        auto after = [&] {  // k has moved past the block
+            if constexpr (fixing) {
+                if (kCkpt && PF < SEG && (k - t_first) % SEG != 0) return;
+                bool same;
+                if constexpr (CPL <= 4)
+                    same = e_old == e_last;
+                else if constexpr (CPL == 8)
+                    same = e_old.x == e_last.x && e_old.y == e_last.y;
+                else
+                    same = e_old.x == e_last.x && e_old.y == e_last.y && e_old.z == e_last.z && e_old.w == e_last.w;
+                agreed = __builtin_amdgcn_ballot_w64(!same) == 0;
+            }
+        };
+        while (k < end && k + PF <= steps && !agreed) {
+            int fast = (min(end, steps) - k) / PF;
+            if (k + fast * PF + PF > steps) fast -= 1;
+            if constexpr (KIND == kDiag) {
+                // no group restarts or wraps, neither in a block nor in the
+                // steps it loads: columns 1 .. W - S - 1 for group 0
+                constexpr int S = 64 / G;
+                const int inner = rx > 0 ? (cur.x >= 1 ? (W - S - cur.x) / PF - 1 : 0) : (cur.x < W - S ? cur.x / PF - 1 : 0);
+                fast = min(fast, inner);
+            }
+            if constexpr (FUSED) fast = 0;
+            if (kCkpt && k < 0) fast = 0;
+            for (int i = 0; i < fast && !agreed; ++i) {
+                before();
+                chunk_fast(fix);
+                after();
+            }
+            if (k < end && k + PF <= steps && !agreed) {
+                before();
+                chunk_any(std::true_type{}, fix);
+                after();
+            }
         }
-    } else if constexpr (!FUSED) {
-        while (kCkpt && k < 0 && k + PF <= steps) chunk_any(std::true_type{});
-        while (k + 2 * PF <= steps) chunk_fast();
+        return agreed;
+    };
+    // The conditional steps of the slice's last, partial block come after the
+    // loops: a way back from them would make the compiler wait in the loops
+    // for loads that may be recent.
+    if constexpr (SPLIT) {
+        bool agreed = blocks_to(seg_end, std::false_type{});
+        while (!agreed && seg_end < steps) {
+            split.next_round();
+            seg_end += seg_len;
+            agreed = blocks_to(seg_end, std::true_type{});
+        }
+        if (!agreed && k < steps) chunk_any(std::false_type{}, std::false_type{});
+        split.finish();
+    } else {
+        blocks_to(steps, std::false_type{});
+        if (k < steps) chunk_any(std::false_type{}, std::false_type{});
     }
-    while (k < steps) chunk_any(std::false_type{});
 }
 
 // ---------------------------------------------------------------------------

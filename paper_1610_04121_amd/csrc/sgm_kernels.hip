@@ -321,6 +321,28 @@ void default_lanes(const Plan& p, int* gh, int* gv) {
         if ((sh[0] < 64 || p.n_paths == 8) && fill(sh[0], sh[1]) > 1.05 * fill(*gh, *gv)) set(sh[0], sh[1]);
 }
 
+// Wavefronts per slice (dev::Split).  Splitting divides the dependent chain
+// and costs the steps until the segments' values meet, so it pays where the
+// longest chain takes well over the time of the launch's bytes.  Estimates: a
+// step 45 ns + 6 per level of a lane (72 ns at 4, 93 at 8), bytes at 6.3 TB/s.
+// Whole calls, unsplit and split (us): 320x240, D = 64, 4 paths (chain over
+// bytes 3.6) 44.0, 35.2 in 4; 1280x720, D = 64, 4 paths (1.6) 155, 140 in 2;
+// 1242x375, D = 128, 4 paths (1.5) 160, 138 in 2; 640x480, D = 128, 2 paths
+// (2.4) 85, 78 in 4; but 800x600, D = 128, 4 paths (1.0) 136, 143; with 256
+// levels 320x240, 4 paths (1.3) 60, 68 and 640x480, 2 paths (1.3) 114, 126.
+// With 8 paths the wavefronts fill the device (160x120, D = 128: 37, 43), and
+// short slices do not repay the rounds (96x64, D = 128: 25.0, 26.4).
+static int slice_segments(const Plan& p, int gh, int gv, bool checkpoints) {
+    if (p.l16 || fused_aggregation(p) || p.n_paths == 8 || std::max(p.W, p.H) < 160) return 1;
+    auto chain_ns = [&](int steps, int lanes) { return steps * (45.0 + 6.0 * (p.Dp / lanes)); };
+    const double chain = std::max(chain_ns(p.W, gh), chain_ns(p.H, gv));
+    const int horiz = p.n_paths == 2 ? 1 : 2, stored = checkpoints ? p.n_paths - horiz : p.n_paths;
+    const double bytes = (p.lr_full ? 2.0 : 1.0) * p.W * p.H * p.Dp * (p.n_paths + stored + (checkpoints ? 0.1 : 0.0));
+    const double ratio = chain / (bytes / 6300.0);  // 6.3 TB/s = 6300 bytes per ns
+    if (ratio < (p.Dp == 256 ? 1.5 : 1.4)) return 1;
+    return ratio > 2.3 ? 4 : 2;
+}
+
 // (it stores L_r itself, which byte planes hold up to Cmax + pmax = 255)
 bool fused_aggregation(const Plan& p) { return p.fused && !p.lr_full && !p.adaptive && (p.l16 || !p.wide); }
 
@@ -335,6 +357,7 @@ hipError_t launch_aggregate(const Plan& p, const Workspace& ws, hipStream_t stre
     a.ckpt = checkpoints ? 1 : 0;
     a.gh = gh;
     a.gv = gv;
+    a.split = slice_segments(p, gh, gv, checkpoints);
     // the store policy is an instruction operand: a second instantiation of
     // the plain (stored-cost, constant-P2) kernels
     const AggVariant v{p.l16, fused_aggregation(p), p.adaptive, p.nt_store && !p.adaptive && !fused_aggregation(p)};
