@@ -52,31 +52,35 @@ __global__ __launch_bounds__(256) void census_batch_kernel(const BatchItem* item
     }
 }
 
-// Blocks 0 .. nx * H - 1 of a pair make its cost volume; with the full
+// Units 0 .. nx * H - 1 of a pair make its cost volume; with the full
 // left-right check, the next nx * H make the right-base costs.
-template <bool RB>
-__device__ inline void cost_batch_block(const BatchItem& it, int bx, int y, uint64_t* smem) {
+template <bool RB, int AUX>
+__device__ inline void cost_batch_unit(const BatchItem& it, int ux, int y, int lane, uint64_t* smem) {
     const CostArgs a = RB ? CostArgs{it.census_r, it.census_l, it.cost_r, it.W, it.H, it.D, it.Dp, it.cmax}
                           : CostArgs{it.census_l, it.census_r, it.cost, it.W, it.H, it.D, it.Dp, it.cmax};
     if (it.Dp == 64)
-        cost_block<RB, 64>(a, bx, y, smem);
+        cost_unit<RB, 64, 8, AUX>(a, ux, y, lane, smem);
     else if (it.Dp == 128)
-        cost_block<RB, 128>(a, bx, y, smem);
+        cost_unit<RB, 128, 8, AUX>(a, ux, y, lane, smem);
     else
-        cost_block<RB, 256>(a, bx, y, smem);
+        cost_unit<RB, 256, 8, AUX>(a, ux, y, lane, smem);
 }
 
-__global__ __launch_bounds__(kCostThreads) void cost_batch_kernel(const BatchItem* items, int n) {
-    extern __shared__ __align__(16) uint64_t cost_smem[];
+template <int AUX>
+__global__ __launch_bounds__(kCostThreads) void cost_batch_kernel(const BatchItem* items, int n, int per_wave) {
+    constexpr int kWaves = kCostThreads / 64;
+    __shared__ uint64_t words[kWaves][CostUnit<256, 8>::words];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int b = blockIdx.x;
     const BatchItem& it = items[find_item<&BatchItem::cost_blk0>(items, n, b)];
-    int local = b - it.cost_blk0;
-    const int nx = (it.W + kCostTX - 1) / kCostTX;
-    if (local < nx * it.H) {
-        cost_batch_block<false>(it, local % nx, local / nx, cost_smem);
-    } else {
-        local -= nx * it.H;
-        cost_batch_block<true>(it, local % nx, local / nx, cost_smem);
+    const int px = cost_unit_px(it.Dp, 8), nx = (it.W + px - 1) / px, per_map = nx * it.H;
+    const int first = (b - it.cost_blk0) * kWaves * per_wave + wave;
+    const int end = min(it.cost_r ? 2 * per_map : per_map, first + kWaves * per_wave);
+    for (int unit = first; unit < end; unit += kWaves) {
+        if (unit < per_map)
+            cost_batch_unit<false, AUX>(it, unit % nx, unit / nx, lane, words[wave]);
+        else
+            cost_batch_unit<true, AUX>(it, (unit - per_map) % nx, (unit - per_map) / nx, lane, words[wave]);
     }
 }
 
@@ -86,6 +90,12 @@ __global__ __launch_bounds__(256) void post_batch_kernel(const BatchItem* items,
     const BatchItem& it = items[find_item<&BatchItem::post_blk0>(items, n, b)];
     PostArgs a{it.dl, it.dr, it.out, it.W, it.H, it.median, it.lrcheck, it.thr, it.subpixel};
     post_row(a, b - it.post_blk0, post_smem);
+}
+
+// Units of a pair's cost volumes.
+size_t cost_unit_count(const Plan& p) {
+    const size_t px = cost_unit_px(p.Dp, 8);
+    return (p.lr_full ? 2 : 1) * ((p.W + px - 1) / px) * p.H;
 }
 
 size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
@@ -231,7 +241,9 @@ struct BatchLaunch {
     std::vector<BatchItem> desc;
     std::vector<WorkItem> work;
     size_t census_blocks = 0, cost_blocks = 0, post_blocks = 0;
-    size_t cost_smem = 0, post_smem = 0;
+    int cost_per_wave = 1;   // units a wavefront of the cost launch takes
+    bool cost_nt = false;    // its stores non-temporal
+    size_t post_smem = 0;
     // The row kernel is one launch per variant (padded range, path count,
     // plane type): pairs of a variant follow each other in desc.
     struct Rows {
@@ -257,7 +269,7 @@ int batch_build(const BatchParams& bp, const Plan* plans, uint8_t* const* ws_bas
     desc.assign(n, BatchItem{});
     work.clear();
     const bool generic = !(bp.cw == 9 && bp.ch == 7);
-    size_t cost_smem = 0, post_smem = 0;
+    size_t post_smem = 0;
     bool any_adapt = false;
     // the pairs in the order of their row-kernel variants
     auto variant = [&](int i) {
@@ -268,6 +280,16 @@ int batch_build(const BatchParams& bp, const Plan* plans, uint8_t* const* ws_bas
     for (int i = 0; i < n; ++i) order[i] = i;
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return variant(a) < variant(b); });
     B.rows.clear();
+    // Cost volumes: 8-pixel units as in the single-pair launch.  From 16
+    // wavefronts per SIMD on, a wavefront takes two units for one look at the
+    // table (64 pairs, 316000 units: 711 us, one unit 740, four 719).
+    size_t cost_units = 0, cost_bytes = 0;
+    for (int i = 0; i < n; ++i) {
+        cost_units += cost_unit_count(plans[i]);
+        cost_bytes += (size_t)(plans[i].lr_full ? 2 : 1) * plans[i].W * plans[i].H * plans[i].Dp;
+    }
+    B.cost_per_wave = cost_units >= 16384 ? 2 : 1;
+    B.cost_nt = cost_bytes > (size_t)kMallBytes;  // the policy of launch_cost
     long long waves16 = 0;  // wavefronts of the aggregation at 16 lanes a slice
     for (int i = 0; i < n; ++i)
         for (int r = 0; r < plans[i].n_paths; ++r)
@@ -317,7 +339,8 @@ int batch_build(const BatchParams& bp, const Plan* plans, uint8_t* const* ws_bas
         census_blocks += generic ? (size_t)2 * ((p.W + 15) / 16) * ((p.H + 15) / 16)
                                  : (size_t)2 * ((p.W + kCenTX - 1) / kCenTX) * ((p.H + kCenTY - 1) / kCenTY);
         d.cost_blk0 = (int)cost_blocks;
-        cost_blocks += (size_t)nsgm * ((p.W + kCostTX - 1) / kCostTX) * p.H;
+        const size_t cost_per = (size_t)(kCostThreads / 64) * B.cost_per_wave;
+        cost_blocks += (cost_unit_count(p) + cost_per - 1) / cost_per;
         if (i == 0 || variant(src) != variant(order[i - 1]))
             B.rows.push_back({p.Dp, i, 0, RowVariant{p.n_paths, p.l16, false, 2 * p.pmax <= 255, p.subpixel}, 0, 0, 1});
         BatchLaunch::Rows& rw = B.rows.back();
@@ -328,8 +351,6 @@ int batch_build(const BatchParams& bp, const Plan* plans, uint8_t* const* ws_bas
         rw.waves = std::max(rw.waves, row_waves(p.W, p.Dp, p.l16));
         d.post_blk0 = (int)post_blocks;
         if (p.median || p.lrcheck) post_blocks += p.H;
-        const int nright = kCostTX + p.D - 1;
-        cost_smem = std::max(cost_smem, 8 * (size_t)((kCostTX + nright + 1) & ~1) + (size_t)kCostTX * (p.Dp + 16));
         if (p.lrcheck) post_smem = std::max(post_smem, 2 * (size_t)p.W);
         for (int sg = 0; sg < nsgm; ++sg)
             for (int r = 0; r < p.n_paths; ++r) {
@@ -410,7 +431,6 @@ int batch_build(const BatchParams& bp, const Plan* plans, uint8_t* const* ws_bas
     B.census_blocks = census_blocks;
     B.cost_blocks = cost_blocks;
     B.post_blocks = post_blocks;
-    B.cost_smem = cost_smem;
     B.post_smem = post_smem;
     return SGM_OK;
 }
@@ -420,8 +440,7 @@ hipError_t batch_launch(const BatchParams& bp, const BatchLaunch& B, const Batch
     const int n = (int)B.desc.size();
     hipLaunchKernelGGL(census_batch_kernel, dim3((unsigned)B.census_blocks), dim3(256), 0, s, d_items, n,
                        B.generic ? 1 : 0, (bp.cw - 1) / 2, (bp.ch - 1) / 2, counter);
-    hipLaunchKernelGGL(cost_batch_kernel, dim3((unsigned)B.cost_blocks), dim3(kCostThreads), B.cost_smem, s, d_items,
-                       n);
+    hipLaunchKernelGGL(B.cost_nt ? cost_batch_kernel<kStoreNT> : cost_batch_kernel<kStoreSc1>, dim3((unsigned)B.cost_blocks), dim3(kCostThreads), 0, s, d_items, n, B.cost_per_wave);
     const int nquads = (int)(B.work.size() / kQuad);
     (B.any_adapt ? launch_batch_agg_adapt : launch_batch_agg)(B.nt, B.blocks, d_items, d_work, nquads, counter, bp.P1,
                                                               bp.P2, s);

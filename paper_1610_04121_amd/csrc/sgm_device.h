@@ -29,13 +29,15 @@ constexpr uint32_t kPadCost = 3;
 __device__ inline int clampi(int v, int lo, int hi) { return v < lo ? lo : (v > hi ? hi : v); }
 
 // 16-byte store at byte offset `ofs` of [base, base + bytes) through a
-// range-checked buffer resource, with device scope (sc1): measured faster
-// than plain stores for the cost volume, whose wavefronts store contiguous
-// runs (whole lines).
-__device__ inline void store16_sc1(void* base, uint32_t bytes, uint32_t ofs, uint4 v) {
+// range-checked buffer resource, with device scope (sc1) or non-temporal:
+// measured faster than plain stores for the cost volume (640x480, D = 128:
+// sc1 12.1 us, plain 15.5; 1920x1080, D = 256: 115, 116, non-temporal 93).
+constexpr int kStoreNT = 2, kStoreSc1 = 16;
+template <int AUX = kStoreSc1>
+__device__ inline void store16(void* base, uint32_t bytes, uint32_t ofs, uint4 v) {
     const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(base, 0, (int)bytes, 0x00020000);
     __builtin_amdgcn_raw_buffer_store_b128((unsigned __attribute__((ext_vector_type(4)))){v.x, v.y, v.z, v.w}, r, ofs,
-                                           0, 16);
+                                           0, AUX);
 }
 
 // ---------------------------------------------------------------------------
@@ -231,17 +233,30 @@ __device__ inline void census_generic_block(const CensusArgs& a, int rx, int ry,
 }
 
 // ---------------------------------------------------------------------------
-// Matching cost (Eq. 2).  One block per (row y, run of 64 base pixels).  The
-// census words of the run and of the match run from x0 - (D-1) on are staged
-// in LDS.  Lane l of every wavefront is pixel x0 + l, so the match words a
-// wavefront reads for one disparity are consecutive (no bank conflicts) and
-// their addresses differ by constants (immediate offsets).  Each wavefront
-// computes runs of 16 disparities, writes them to an LDS tile [64][Dp + 16]
-// (the padding spreads rows over banks), and the block then copies the tile
-// to the cost volume with contiguous 16-byte stores.
+// Matching cost (Eq. 2).  One wavefront per (row y, unit of PX base
+// pixels).  A lane makes the costs of 16 consecutive disparities of one
+// pixel after another, RUN pixels in all: 16 lanes (8, 4) hold the 256 (128, 64)
+// levels of a pixel, and the wavefront works on pixels RUN apart.  From one pixel
+// to the next a lane's 16 match words move on by one, so a step reads one match
+// and one base word from LDS for 16 costs, and its 16 costs are one 16-byte
+// store at the place they belong.  The unit's words are staged by the
+// wavefront for itself: no barrier, and a block is four independent units.
+//
+// The VALU and the stores bound it about alike: two xor, two counting
+// instructions and a shift per cost, against one byte.  1920x1080, D = 256: 88
+// us (6.0 TB/s of costs; before, with a lane per pixel, a tile in LDS and a
+// copy out of it, 113); 640x480, D = 128: 11.7 us (12.7); 64 mixed pairs,
+// 2.6 GB: 711 us (967).
 // ---------------------------------------------------------------------------
-constexpr int kCostTX = 64;
-constexpr int kCostThreads = 256;  // block size of every launch of cost_block
+constexpr int kCostThreads = 256;  // block size of every launch of cost_unit
+template <int DP, int RUN>
+struct CostUnit {
+    static constexpr int G = DP / 16;                  // lanes per pixel
+    static constexpr int PX = 64 / G * RUN;            // pixels per unit
+    static constexpr int N = 2 * PX + DP;              // words staged: PX base, PX + DP match
+    static constexpr int words = N / RUN * (RUN + 1);  // in LDS: one word of padding after every RUN
+};
+__host__ __device__ constexpr int cost_unit_px(int Dp, int run) { return 64 / (Dp / 16) * run; }
 
 struct CostArgs {
     const uint64_t* cl;
@@ -252,124 +267,111 @@ struct CostArgs {
 
 // RB = false: base words cl = left view, match words cr = right view at x - d
 // (Eq. 2).  RB = true: base = right view, match = left view at x + d (the
-// right-base costs of the full left-right check).  DP = a.Dp (64, 128 or
-// 256) as a constant, so the chunk and copy loops unroll and the tile pitch
-// is an immediate.
-template <bool RB, int DP>
-__device__ inline void cost_block(const CostArgs& a, int bx, int y, uint64_t* cw_smem) {
-    static_assert(DP == 64 || DP == 128 || DP == 256, "padded disparity range");
-    const int x0 = bx * kCostTX;
-    const int D = a.D;
-    constexpr int Dp = DP;
-    const int nright = kCostTX + D - 1;
-    constexpr int tpitch = Dp + 16;  // bytes per tile row
-    uint64_t* cl = cw_smem;
-    // cr[i] = match word of column xm0 + i
-    uint64_t* cr = cl + kCostTX;
-    const int xm0 = RB ? x0 : x0 - (D - 1);
-    // the tile starts on a 16-byte boundary (an even number of words)
-    uint8_t* tile = reinterpret_cast<uint8_t*>(cl + ((kCostTX + nright + 1) & ~1));
-    const uint64_t* gl = a.cl + (size_t)y * a.W;
-    const uint64_t* gr = a.cr + (size_t)y * a.W;
-    // Every global load is issued before the first LDS store, so the loads'
-    // latencies overlap instead of adding up.  The block has kCostThreads
-    // threads: one base word each for the first 64, and the match words
-    // (nright <= kCostTX + 255 < 2 * kCostThreads) in two rounds.
-    {
-        const int t = threadIdx.x;
-        uint64_t vl = 0, vr[2] = {0, 0};
-        const bool hl = t < kCostTX && x0 + t < a.W;
-        if (hl) vl = gl[x0 + t];
-        bool hr[2];
+// right-base costs of the full left-right check).  DP = a.Dp (64, 128 or 256).
+// smem: CostUnit::words words of this wavefront's own.  AUX: store policy.
+template <bool RB, int DP, int RUN, int AUX>
+__device__ inline void cost_unit(const CostArgs& a, int ux, int y, int lane, uint64_t* smem) {
+    using U = CostUnit<DP, RUN>;
+    constexpr int G = U::G, PX = U::PX;
+    const int x0 = ux * PX, W = a.W, D = a.D;
+    // item n of the unit is base word x0 + n (n < PX) or match word
+    // xm0 + n - PX, at LDS word n + n / RUN: the lanes of a step read words a
+    // multiple of RUN apart, which the padding spreads over the banks
+    const int xm0 = RB ? x0 : x0 - DP;
+    const uint64_t* gl = a.cl + (size_t)y * W;
+    const uint64_t* gr = a.cr + (size_t)y * W;
+    constexpr int kLoads = (U::N + 63) / 64;
+    uint64_t v[kLoads];
 #pragma unroll
-        for (int k = 0; k < 2; ++k) {
-            const int i = t + kCostThreads * k, xr = xm0 + i;
-            hr[k] = i < nright && xr >= 0 && xr < a.W;
-            if (hr[k]) vr[k] = gr[xr];
-        }
-        if (hl) cl[t] = vl;
-#pragma unroll
-        for (int k = 0; k < 2; ++k)
-            if (hr[k]) cr[t + kCostThreads * k] = vr[k];
+    for (int k = 0; k < kLoads; ++k) {
+        const int n = lane + 64 * k;
+        const bool base = n < PX;
+        const int x = base ? x0 + n : xm0 + n - PX;
+        v[k] = 0;
+        if (x >= 0 && x < W && n < U::N) v[k] = (base ? gl : gr)[x];
     }
-    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kLoads; ++k) {
+        const int n = lane + 64 * k;
+        if (n < U::N) smem[n + n / RUN] = v[k];
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
 
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int x = x0 + lane;
-    const uint64_t base = cl[lane];
-    constexpr int nchunks = Dp >> 4;
-    constexpr int nwaves = kCostThreads / 64;
+    const int g = lane / G, q = lane % G;
+    constexpr int PR = RUN + 1, HOP = 16 / RUN;
+    const uint64_t* bl = smem + PR * g;
+    // match word of step s, disparity 16q + j: column x - 16q - j, item
+    // PX + DP + RUN g - 16q + (s - j) (left base), or x + 16q + j, item
+    // PX + RUN g + 16q + (s + j)
+    const uint64_t* ml = smem + PR * (PX / RUN + (RB ? g + HOP * q : DP / RUN + g - HOP * q));
+    auto word = [&](int o) { return ml[PR * ((o + 16) / RUN - HOP) + (o + 16) % RUN]; };  // o >= -15
+    const int col = x0 + RUN * g + (RB ? 16 * q : -16 * q);  // match column of s = j = 0
+    uint8_t* const row = a.cost + (size_t)y * W * DP;
+    const uint32_t ofs = (uint32_t)((x0 + RUN * g) * DP + 16 * q);  // past the row's end: dropped
+
+    auto run = [&](auto general) {
+        constexpr bool GENERAL = decltype(general)::value;
+        // Levels d >= D get kPadCost and match pixels outside the image Cmax.
+        // Both are byte masks over the 16 levels; the second moves on by a
+        // byte a step (the last levels of a lane are outside, fewer of them
+        // with every step to the right and more with the right base), so it
+        // extends past the 16 by the bytes that move in.
+        constexpr int E = (RUN + 3) / 4;
+        // 0xFF in the bytes of word k from byte n on (bytes counted from word 0)
+        auto from = [](int n, int k) { return (uint32_t)(~0ull << (8 * min(max(n - 4 * k, 0), 4))); };
+        uint32_t pad[4], out[4 + E];  // out[k]: word k - E (left base) or k of the mask
+        if constexpr (GENERAL) {
 #pragma unroll
-    for (int it = 0; it < nchunks / nwaves; ++it) {
-        const int ch = wave + nwaves * it;
-        const int d0 = 16 * ch;
-        // match word of disparity d0 + j: cr[lane + D - 1 - d0 - j] (left
-        // base), cr[lane + d0 + j] (right base)
-        auto word = [&](int j) -> uint64_t { return RB ? cr[lane + d0 + j] : cr[lane + D - 1 - d0 - j]; };
-        // all 16 disparities inside the image for every lane of the run
-        const bool inside = RB ? (x0 + kCostTX - 1 + d0 + 15 < a.W) : (x0 >= d0 + 15);
-        uint32_t w[4];
-        if (inside && d0 + 16 <= D) {
+            for (int k = 0; k < 4; ++k) pad[k] = from(D - 16 * q, k);
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                uint32_t wd = 0;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) wd |= (uint32_t)__popcll(base ^ word(4 * q + j)) << (8 * j);
-                w[q] = wd;
-            }
-        } else if (d0 + 16 <= D) {
-            // a run at the image border: every lane's LDS word exists, so
-            // every lane takes the popcount and a select puts Cmax where the
-            // match pixel is outside the image (no per-lane branch)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                uint32_t wd = 0;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int d = d0 + 4 * q + j;
-                    const uint32_t pc = (uint32_t)__popcll(base ^ word(4 * q + j));
-                    const bool out = RB ? x + d >= a.W : x - d < 0;
-                    wd |= (out ? (uint32_t)a.cmax : pc) << (8 * j);
-                }
-                w[q] = wd;
-            }
-        } else {  // the chunk holding D - 1 and the padded levels
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                uint32_t wd = 0;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int d = d0 + 4 * q + j;
-                    uint32_t c = kPadCost;  // padded levels d >= D
-                    if (d < D) {
-                        const uint32_t pc = (uint32_t)__popcll(base ^ word(4 * q + j));
-                        const bool out = RB ? x + d >= a.W : x - d < 0;
-                        c = out ? (uint32_t)a.cmax : pc;
-                    }
-                    wd |= c << (8 * j);
-                }
-                w[q] = wd;
-            }
+            for (int k = 0; k < 4 + E; ++k) out[k] = RB ? from(W - col, k) : from(col + 1, k - E);
         }
-        *reinterpret_cast<uint4*>(tile + lane * tpitch + d0) = make_uint4(w[0], w[1], w[2], w[3]);
-    }
-    __syncthreads();
-    const int npx = min(kCostTX, a.W - x0);
-    uint8_t* dst = a.cost + ((size_t)y * a.W + x0) * Dp;
-    // kCostTX * nchunks 16-byte pieces, nchunks / nwaves per thread: all LDS
-    // reads first, then the stores
-    constexpr int nper = kCostTX * nchunks / kCostThreads;
-    uint4 v[nper];
+        uint64_t w[16];  // the window: word o in slot o & 15
 #pragma unroll
-    for (int j = 0; j < nper; ++j) {
-        const int c = threadIdx.x + kCostThreads * j;
-        v[j] = *reinterpret_cast<const uint4*>(tile + (c / nchunks) * tpitch + 16 * (c % nchunks));
-    }
+        for (int j = 0; j < 16; ++j) w[(RB ? j : -j) & 15] = word(RB ? j : -j);
 #pragma unroll
-    for (int j = 0; j < nper; ++j) {
-        const int c = threadIdx.x + kCostThreads * j;
-        if (c < npx * nchunks) store16_sc1(dst, (uint32_t)(npx * Dp), 16u * (uint32_t)c, v[j]);
-    }
+        for (int s = 0; s < RUN; ++s) {
+            const uint64_t b = bl[s];
+            uint32_t c[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                c[k] = 0;
+#pragma unroll
+                for (int i = 3; i >= 0; --i) {
+                    const int j = 4 * k + i;
+                    const uint64_t x = b ^ w[(RB ? s + j : s - j) & 15];
+                    c[k] = (uint32_t)__popc((uint32_t)(x >> 32)) + ((uint32_t)__popc((uint32_t)x) + (c[k] << 8));
+                }
+                if constexpr (GENERAL) {
+                    const uint32_t o = out[RB ? k : k + E];
+                    c[k] = ((uint32_t)a.cmax * 0x01010101u & o) | (c[k] & ~o);
+                    c[k] = (kPadCost * 0x01010101u & pad[k]) | (c[k] & ~pad[k]);
+                }
+            }
+            if (s + 1 < RUN) {
+                const int o = RB ? s + 16 : s + 1;
+                w[o & 15] = word(o);
+                if constexpr (GENERAL) {
+                    if constexpr (RB) {
+#pragma unroll
+                        for (int k = 0; k < 4 + E; ++k)
+                            out[k] = __builtin_amdgcn_alignbit(k + 1 < 4 + E ? out[k + 1] : ~0u, out[k], 8);
+                    } else {
+#pragma unroll
+                        for (int k = 3 + E; k >= 0; --k)
+                            out[k] = __builtin_amdgcn_alignbit(out[k], k > 0 ? out[k - 1] : 0u, 24);
+                    }
+                }
+            }
+            store16<AUX>(row, (uint32_t)(W * DP), ofs + (uint32_t)(s * DP), make_uint4(c[0], c[1], c[2], c[3]));
+        }
+    };
+    const bool border = RB ? x0 + PX - 1 + D - 1 >= W : x0 < D - 1;
+    if (border || D < DP)
+        run(std::true_type{});
+    else
+        run(std::false_type{});
 }
 
 // ---------------------------------------------------------------------------
@@ -538,7 +540,7 @@ __device__ inline void census_cost_block(const CensusCostArgs& a, int bx, int y,
         uint8_t* dst = a.cost + ((size_t)y * a.W + xr0) * Dp;
         for (int c = threadIdx.x; c < npx * nchunks; c += blockDim.x) {
             const int px = c >> lg, k = c & (nchunks - 1);
-            store16_sc1(dst, (uint32_t)(npx * Dp), 16u * (uint32_t)c,
+            store16(dst, (uint32_t)(npx * Dp), 16u * (uint32_t)c,
                         *reinterpret_cast<const uint4*>(tile + px * L.tpitch + 16 * k));
         }
     }

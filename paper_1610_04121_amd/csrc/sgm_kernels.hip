@@ -28,10 +28,21 @@ __global__ __launch_bounds__(256) void census_cost_kernel(CensusCostArgs a) {
     census_cost_block(a, blockIdx.x, blockIdx.y, cc_smem);
 }
 
-template <bool RB, int DP>
+template <bool RB, int DP, int RUN, int AUX>
 __global__ __launch_bounds__(kCostThreads) void cost_kernel(CostArgs a) {
-    extern __shared__ __align__(16) uint64_t cost_smem[];
-    cost_block<RB, DP>(a, blockIdx.x, blockIdx.y, cost_smem);
+    using U = CostUnit<DP, RUN>;
+    __shared__ uint64_t words[kCostThreads / 64][U::words];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int nx = (a.W + U::PX - 1) / U::PX;
+    const int unit = blockIdx.x * (kCostThreads / 64) + wave;
+    if (unit < nx * a.H) cost_unit<RB, DP, RUN, AUX>(a, unit % nx, unit / nx, threadIdx.x & 63, words[wave]);
+}
+
+template <bool RB, int RUN, int AUX>
+void launch_cost_t(const CostArgs& a, hipStream_t stream) {
+    const int px = cost_unit_px(a.Dp, RUN), units = (a.W + px - 1) / px * a.H, per = kCostThreads / 64;
+    auto k = a.Dp == 64 ? cost_kernel<RB, 64, RUN, AUX> : a.Dp == 128 ? cost_kernel<RB, 128, RUN, AUX> : cost_kernel<RB, 256, RUN, AUX>;
+    hipLaunchKernelGGL(k, dim3((units + per - 1) / per), dim3(kCostThreads), 0, stream, a);
 }
 
 template <typename LT, bool NT, bool FOLD>
@@ -219,15 +230,27 @@ hipError_t launch_matching_cost(const Plan& p, const Workspace& ws, const uint8_
 }
 
 hipError_t launch_cost(const Plan& p, const Workspace& ws, hipStream_t stream, bool right_base) {
-    const int nright = kCostTX + p.D - 1;
-    const size_t smem = 8 * (size_t)((kCostTX + nright + 1) & ~1) + (size_t)kCostTX * (p.Dp + 16);
-    dim3 grid((p.W + kCostTX - 1) / kCostTX, p.H);
     if (right_base && !ws.cost_r) return hipErrorInvalidValue;
     const CostArgs a = right_base ? CostArgs{ws.census_r, ws.census_l, ws.cost_r, p.W, p.H, p.D, p.Dp, p.cmax}
                                   : CostArgs{ws.census_l, ws.census_r, ws.cost, p.W, p.H, p.D, p.Dp, p.cmax};
-    auto k = right_base ? (p.Dp == 64 ? cost_kernel<true, 64> : p.Dp == 128 ? cost_kernel<true, 128> : cost_kernel<true, 256>)
-                        : (p.Dp == 64 ? cost_kernel<false, 64> : p.Dp == 128 ? cost_kernel<false, 128> : cost_kernel<false, 256>);
-    hipLaunchKernelGGL(k, grid, dim3(kCostThreads), smem, stream, a);
+    // Pixels per lane: 8; 2 where 8 leave at most one wavefront per SIMD, so
+    // that the launch is a shorter chain (96x64, D = 32: 3.2 and 4.3 us).  With
+    // every SIMD busy the staging of the match words counts (1600x1200,
+    // D = 128: 8 pixels 42 us, 4 45, 2 65).
+    const int px = cost_unit_px(p.Dp, 8);
+    const bool few = (long long)((p.W + px - 1) / px) * p.H <= 1024;
+    // A volume larger than the memory-side cache is written past it: the
+    // aggregation cannot find it there (1920x1080, D = 256, 531 MB: 88 us, with
+    // sc1 108); smaller ones stay (1280x720, D = 64: sc1 13.8 us, 17.4).
+    const bool nt = (long long)(p.lr_full ? 2 : 1) * p.W * p.H * p.Dp > kMallBytes;
+    if (right_base)
+        few  ? launch_cost_t<true, 2, kStoreSc1>(a, stream)
+        : nt ? launch_cost_t<true, 8, kStoreNT>(a, stream)
+             : launch_cost_t<true, 8, kStoreSc1>(a, stream);
+    else
+        few  ? launch_cost_t<false, 2, kStoreSc1>(a, stream)
+        : nt ? launch_cost_t<false, 8, kStoreNT>(a, stream)
+             : launch_cost_t<false, 8, kStoreSc1>(a, stream);
     return hipGetLastError();
 }
 
