@@ -690,6 +690,20 @@ __device__ inline uint32_t group_min(uint32_t v, FILL fill = FILL{}) {
     return v;
 }
 
+// The same reduction with a bitwise or (G = 16 or 32).
+template <int G>
+__device__ inline uint32_t group_or(uint32_t v) {
+    v |= (uint32_t)__builtin_amdgcn_mov_dpp((int)v, kDppQuadPerm1032, 0xF, 0xF, true);
+    v |= (uint32_t)__builtin_amdgcn_mov_dpp((int)v, kDppQuadPerm2301, 0xF, 0xF, true);
+    v |= (uint32_t)__builtin_amdgcn_mov_dpp((int)v, kDppRowHalfMirror, 0xF, 0xF, true);
+    v |= (uint32_t)__builtin_amdgcn_mov_dpp((int)v, kDppRowMirror, 0xF, 0xF, true);
+    if constexpr (G == 32) {
+        const auto sw = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+        v = (uint32_t)sw[0] | (uint32_t)sw[1];
+    }
+    return v;
+}
+
 // Raw cost bytes of one lane for one step: CPL bytes.
 template <int CPL> struct Raw;
 template <> struct Raw<2> { using T = uint16_t; };

@@ -296,7 +296,7 @@ __device__ inline void row_block(const RowArgs& a, int y, uint32_t* keyR_smem, c
         uint32_t col[CPL];  // right view: smallest keys of columns x - d
 #pragma unroll
         for (int i = 0; i < CPL; ++i) col[i] = ~0u;
-        uint32_t outl = 0, outr = 0;  // lane j: results of column x0 + j
+        uint32_t outl = 0, outn = 0, outr = 0;  // lane j: results of column x0 + j
 #pragma unroll
         for (int j = SEG - 1; j >= 0; --j) {
             __builtin_amdgcn_sched_barrier(0);
@@ -350,21 +350,24 @@ __device__ inline void row_block(const RowArgs& a, int y, uint32_t* keyR_smem, c
 #pragma unroll
             for (int i = 1; i < CPL; ++i) best = min(best, key[i]);
             best = group_min<G>(best);
-            uint32_t res = best & 0xFFu;
+            // results enter at lane 0 and move up as the walk goes left
             if constexpr (SUB) {
-                // S(d - 1) and S(d + 1) of the winner d from the lanes that
-                // hold them; the vertex as in wta_cells
-                const int d = (int)res, d0 = q * CPL;
-                uint32_t va = ~0u, vc = ~0u;
+                // the winner's key, and S(d - 1) | S(d + 1) << 16 from the
+                // lanes that hold them; the vertex (a division) is taken once
+                // a unit, by the lane the column ends in
+                const int t = (int)(best & 0xFFu) - q * CPL;
+                uint32_t va = 0, vc = 0;
 #pragma unroll
                 for (int i = 0; i < CPL; ++i) {
-                    if (d0 + i == d - 1) va = key[i] >> 8;
-                    if (d0 + i == d + 1) vc = key[i] >> 8;
+                    if (t == i + 1) va = key[i];
+                    if (t == i - 1) vc = key[i];
                 }
-                if (a.subpixel) res = subpixel_q4(best, group_min<G>(va), group_min<G>(vc), a.D);
+                const uint32_t nb = group_or<G>(__builtin_amdgcn_perm(vc, va, 0x06050201u));
+                outl = (uint32_t)__builtin_amdgcn_update_dpp((int)best, (int)outl, kDppRowShr1, 0xF, 0xF, false);
+                outn = (uint32_t)__builtin_amdgcn_update_dpp((int)nb, (int)outn, kDppRowShr1, 0xF, 0xF, false);
+            } else {
+                outl = (uint32_t)__builtin_amdgcn_update_dpp((int)(best & 0xFFu), (int)outl, kDppRowShr1, 0xF, 0xF, false);
             }
-            // results enter at lane 0 and move up as the walk goes left
-            outl = (uint32_t)__builtin_amdgcn_update_dpp((int)res, (int)outl, kDppRowShr1, 0xF, 0xF, false);
             // the columns take the smaller key; past the row's end (off = ~0)
             // the median leaves them at ~0
             const uint32_t up = from_upper<G>(col[0]) | edge_col;
@@ -376,6 +379,7 @@ __device__ inline void row_block(const RowArgs& a, int y, uint32_t* keyR_smem, c
             }
             outr = (uint32_t)__builtin_amdgcn_update_dpp((int)col[0], (int)outr, kDppRowShr1, 0xF, 0xF, false);
         }
+        if constexpr (SUB) outl = a.subpixel ? subpixel_q4(outl, outn & 0xFFFFu, outn >> 16, a.D) : outl & 0xFFu;
         const bool mine = q < SEG && x0 + q < W;
         // (lanes beyond the segment or the row store outside the buffer)
         __builtin_amdgcn_raw_buffer_store_b16((uint16_t)outl, rd, q < SEG ? 2u * (uint32_t)(x0 + q) : ~1u, 0, 0);
