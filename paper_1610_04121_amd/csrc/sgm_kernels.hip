@@ -351,10 +351,13 @@ void default_lanes(const Plan& p, int* gh, int* gv) {
 // Whole calls, unsplit and split (us): 320x240, D = 64, 4 paths (chain over
 // bytes 3.6) 44.0, 35.2 in 4; 1280x720, D = 64, 4 paths (1.6) 155, 140 in 2;
 // 1242x375, D = 128, 4 paths (1.5) 160, 138 in 2; 640x480, D = 128, 2 paths
-// (2.4) 85, 78 in 4; but 800x600, D = 128, 4 paths (1.0) 136, 143; with 256
-// levels 320x240, 4 paths (1.3) 60, 68 and 640x480, 2 paths (1.3) 114, 126.
-// With 8 paths the wavefronts fill the device (160x120, D = 128: 37, 43), and
-// short slices do not repay the rounds (96x64, D = 128: 25.0, 26.4).
+// (2.4) 85, 77 in 2, 78 in 4; but 800x600, D = 128, 4 paths (1.0) 136, 143;
+// with 256 levels 320x240, 4 paths (1.3) 60, 68 and 640x480, 2 paths (1.3)
+// 114, 126.  With 8 paths the wavefronts fill the device (160x120, D = 128:
+// 37, 43), and short slices do not repay the rounds (96x64, D = 128: 25.0,
+// 26.4).  On unrelated images, where the values never meet, the rounds take
+// the time the split saves and more: 640x480, D = 128, 2 paths 101 (flat
+// images 85); so 2 paths, whose chain is the shorter one, split in 2 at most.
 static int slice_segments(const Plan& p, int gh, int gv, bool checkpoints) {
     if (p.l16 || fused_aggregation(p) || p.n_paths == 8 || std::max(p.W, p.H) < 160) return 1;
     auto chain_ns = [&](int steps, int lanes) { return steps * (45.0 + 6.0 * (p.Dp / lanes)); };
@@ -363,7 +366,7 @@ static int slice_segments(const Plan& p, int gh, int gv, bool checkpoints) {
     const double bytes = (p.lr_full ? 2.0 : 1.0) * p.W * p.H * p.Dp * (p.n_paths + stored + (checkpoints ? 0.1 : 0.0));
     const double ratio = chain / (bytes / 6300.0);  // 6.3 TB/s = 6300 bytes per ns
     if (ratio < (p.Dp == 256 ? 1.5 : 1.4)) return 1;
-    return ratio > 2.3 ? 4 : 2;
+    return ratio > 2.3 && p.n_paths == 4 ? 4 : 2;
 }
 
 // (it stores L_r itself, which byte planes hold up to Cmax + pmax = 255)
