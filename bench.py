@@ -164,15 +164,41 @@ def summarize_trace(csv_path: str, skip_frac: float = 0.2, frames_range=None) ->
             "gap_between_frames_us": med(between) if between else None}
 
 
-def pipeline_bytes(W: int, H: int, Dp: int, P: int, tuning) -> int:
+def row_kernel(W: int, H: int, Dp: int, P: int, tuning) -> bool:
+    """Whether a frame's sum and winner-take-all run in the row kernel (the
+    library's rule: above 72 Mi cell-paths, unless the tuning asks for the
+    fused aggregation, the final pass or the post stage inside the WTA)."""
+    return W * H * Dp * P > 72 << 20 and not any(bool(v) for v in (tuning[2], *tuning[4:6]))
+
+
+def aggregate_bytes(W: int, H: int, Dp: int, P: int, row: bool) -> int:
+    """Bytes of the aggregation launch: the cost volume read and a plane (u8)
+    written per direction; with the row kernel a horizontal direction stores
+    every 16th column only."""
+    N, h = W * H * Dp, 1 if P == 2 else 2
+    return 2 * P * N if not row else P * N + (P - h) * N + h * N // 16
+
+
+def wta_bytes(W: int, H: int, Dp: int, P: int, row: bool) -> int:
+    """Bytes of the sum and winner-take-all: the cost volume and the planes
+    read (with the row kernel the vertical and diagonal ones and the stored
+    columns), two maps out."""
+    N, h = W * H * Dp, 1 if P == 2 else 2
+    return (N + P * N if not row else N + (P - h) * N + h * N // 16) + 4 * W * H
+
+
+def pipeline_bytes(W: int, H: int, Dp: int, P: int, tuning, row: bool = False) -> int:
     """Algorithmic bytes of census, cost, aggregation and WTA for one frame
     (each byte read or written once per kernel that needs it): images in,
     u64 census words of both views, the u8 cost volume, P u8 L_r planes
     written and read back, the raw D_L and D_R maps out.  With the final pass
     (tuning[4]) the last direction's plane is neither written nor read: the
     aggregation launch moves 2 (P - 1) N, the final pass reads the cost
-    volume and the P - 1 planes."""
+    volume and the P - 1 planes.  row: the schedule of the row kernel."""
     px, N = W * H, W * H * Dp
+    if row:
+        census, cost = (0, 2 * px + N) if bool(tuning[3]) else (2 * px + 16 * px, 16 * px + N)
+        return census + cost + aggregate_bytes(W, H, Dp, P, True) + wta_bytes(W, H, Dp, P, True)
     fused, census_cost = bool(tuning[2]), bool(tuning[3])
     if len(tuning) > 4 and bool(tuning[4]) and not fused:
         census, cost = (0, 2 * px + N) if census_cost else (2 * px + 16 * px, 16 * px + N)
@@ -363,7 +389,7 @@ def bench_batch(dev, steps: int, warmup: int = 3, post: bool = False):
         Dp = 64 if it["max_disp"] <= 64 else (128 if it["max_disp"] <= 128 else 256)
         # the batch runs separate census and cost launches; the post stage
         # reads both raw maps' 3x3 neighbourhoods and writes the output
-        alg_bytes += pipeline_bytes(it["w"], it["h"], Dp, it["n_paths"], (0, 0, False, False, False))
+        alg_bytes += pipeline_bytes(it["w"], it["h"], Dp, it["n_paths"], (0, 0, False, False, False), row=True)
         if post:
             alg_bytes += 6 * it["w"] * it["h"]
     b = Batch(synth.P1_DEFAULT, synth.P2_DEFAULT)
@@ -927,15 +953,17 @@ def main():
         extras["copy_gbs"] = round(2 * nb * 10 / (ce0.elapsed_time(ce1) * 1e-3) / 1e9, 1)
         del csrc, cdst
 
-    # the aggregation kernel reads the cost volume (u8) and writes one L_r
-    # plane (u8: Cmax + P2 = 148 < 256) per direction it runs: all of them,
-    # or all but the last with the final pass
+    # the aggregation kernel reads the cost volume (u8) and writes one plane
+    # of L_r - C (u8: at most P2 = 86) per direction it runs: all of them, or
+    # all but the last with the final pass; before the row kernel only every
+    # 16th column of the horizontal ones
     Dp = 64 if D <= 64 else (128 if D <= 128 else 256)
     final_pass = bool(tuning[4]) and not tuning[2]
+    row = row_kernel(W, H, Dp, P, tuning)
     if tuning[2]:  # fused: census words of both views in, L_r out
         agg_bytes = P * W * H * (Dp + 2 * 8)
     else:  # cost volume in, L_r out
-        agg_bytes = (P - 1 if final_pass else P) * W * H * Dp * (1 + 1)
+        agg_bytes = 2 * (P - 1) * W * H * Dp if final_pass else aggregate_bytes(W, H, Dp, P, row)
     agg_ms = stage_ms["aggregate"] / max(ncalls, 1)
     achieved = agg_bytes / (agg_ms * 1e-3) / 1e9
     roof = {"kernel": "aggregate_kernel", "bound": "hbm", "achieved": round(achieved, 1),
@@ -944,19 +972,21 @@ def main():
     if "copy_gbs" in extras:
         roof["measured_copy_gbs"] = extras["copy_gbs"]
         roof["frac_of_measured_copy"] = round(achieved / extras["copy_gbs"], 4)
-    # the winner-take-all stage: the WTA kernel (P planes in, two maps out),
-    # or the final pass (cost volume and P - 1 planes in, two maps out)
+    # the winner-take-all stage: the row kernel, the WTA kernel, or the final
+    # pass (cost volume and P - 1 planes in, two maps out)
     wta_ms = stage_ms["wta"] / max(ncalls, 1)
-    wta_bytes = P * W * H * Dp + 4 * W * H  # P planes, or the cost volume and P - 1 planes
-    wta_gbs = wta_bytes / (wta_ms * 1e-3) / 1e9
-    wta_stage = {"kernel": "final_pass_kernel" if final_pass else "wta_kernel", "alg_bytes_per_launch": wta_bytes,
+    # (census-computing aggregation: its P planes hold L_r, no cost volume)
+    sum_bytes = P * W * H * Dp + 4 * W * H if final_pass or tuning[2] else wta_bytes(W, H, Dp, P, row)
+    wta_gbs = sum_bytes / (wta_ms * 1e-3) / 1e9
+    wta_stage = {"kernel": "final_pass_kernel" if final_pass else "row_kernel" if row else "wta_kernel",
+                 "alg_bytes_per_launch": sum_bytes,
                  "mean_launch_ms": round(wta_ms, 5), "achieved": round(wta_gbs, 1), "unit": "GB/s",
                  "frac": round(wta_gbs / HBM_PEAK_GBS, 4)}
 
     # the whole path from the first census launch to the end of the WTA
     # (median and LR excluded), event-timed like the stages it spans
     pipe_ms = sum(stage_ms[k] for k in ("census_cost", "aggregate", "wta")) / max(ncalls, 1)
-    pipe_bytes = pipeline_bytes(W, H, Dp, P, tuning)
+    pipe_bytes = pipeline_bytes(W, H, Dp, P, tuning, row)
     pipe_gbs = pipe_bytes / (pipe_ms * 1e-3) / 1e9
     pipe = {"stages": "census..wta", "ms_per_frame": round(pipe_ms, 5), "alg_bytes": pipe_bytes,
             "achieved": round(pipe_gbs, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
