@@ -126,7 +126,8 @@ int sgm_compute(sgm_ctx *ctx, const uint8_t *left, const uint8_t *right, uint16_
  *   fused   - bit SGM_TUNE_FUSED_AGG: the aggregation computes the matching
  *   costs from census words itself (no cost volume in memory); otherwise a
  *   cost kernel writes the u8 cost volume C[H][W][Dp] that the aggregation
- *   reads.  Bit SGM_TUNE_FUSED_CENSUS_COST (9x7 windows): that cost volume
+ *   reads; ignored with SGM_LR_FULL or SGM_ADAPTIVE_P2, and where a byte holds
+ *   the largest penalty but not Cmax plus it.  Bit SGM_TUNE_FUSED_CENSUS_COST (9x7 windows): that cost volume
  *   comes from one census + cost launch instead of a census launch and a cost
  *   launch.  Bit SGM_TUNE_FINAL_PASS: the last path direction (right-to-left;
  *   left-to-right with 2 paths) runs fused with the sum over directions and
@@ -202,10 +203,11 @@ typedef struct sgm_batch sgm_batch;
 /* A batch runner on the current HIP device.  NULL on error. */
 sgm_batch *sgm_batch_create(int P1, int P2, int census_w, int census_h);
 
-/* Enqueues all n items on `stream`: one census, one cost, one aggregation,
- * one sum + winner-take-all and one median + LR launch for the whole batch
- * (items with SGM_LR_FULL add their right-base costs, directions and rows to
- * the same launches).
+/* Enqueues all n items on `stream`: one census, one cost, one aggregation and
+ * one median + LR launch for the whole batch, and one sum + winner-take-all
+ * launch per kernel variant in it (padded range, path count, plane type,
+ * sub-pixel; items with SGM_LR_FULL add their right-base costs, directions and
+ * rows to the same launches).
  * The aggregation is a persistent kernel whose wavefronts take (pair,
  * direction, slice group) work items, longest first, from a queue.  The
  * runner keeps a device workspace that grows to the largest batch seen;
