@@ -1063,7 +1063,9 @@ __device__ inline void aggregate_wave(const SliceArgs& a, int first_slice, int l
     Pos cur;
     // a right-to-left walk with checkpoints starts so that its blocks end at
     // multiples of PF and SEG: its first steps (t < 0) repeat the first column
-    // and the path starts after them
+    // and the path starts after them, at t = 0 (step_at_cur; the block that
+    // holds t = 0 takes the general form, also where it is the block's first
+    // step, as after a lead-in of a whole block)
     constexpr int kAlign = PF > SEG ? PF : SEG;
     const int t_first = kCkpt && rx < 0 ? -((kAlign - W % kAlign) % kAlign) : 0;
     // the wavefront's segment: whole blocks [t_begin, seg_end) of the slice
@@ -1472,7 +1474,7 @@ __device__ inline void aggregate_wave(const SliceArgs& a, int first_slice, int l
                 fast = min(fast, inner);
             }
             if constexpr (FUSED) fast = 0;
-            if (kCkpt && k < 0) fast = 0;
+            if (kCkpt && t_first < 0 && k <= 0) fast = 0;
             for (int i = 0; i < fast && !agreed; ++i) {
                 before();
                 chunk_fast(fix);
