@@ -203,11 +203,12 @@ typedef struct sgm_batch sgm_batch;
 /* A batch runner on the current HIP device.  NULL on error. */
 sgm_batch *sgm_batch_create(int P1, int P2, int census_w, int census_h);
 
-/* Enqueues all n items on `stream`: one census, one cost, one aggregation and
- * one median + LR launch for the whole batch, and one sum + winner-take-all
- * launch per kernel variant in it (padded range, path count, plane type,
- * sub-pixel; items with SGM_LR_FULL add their right-base costs, directions and
- * rows to the same launches).
+/* Enqueues all n items on `stream`: one census, one cost, one aggregation, one
+ * sum + winner-take-all and one median + LR launch for the whole batch; with
+ * more than 72 MiB of direction volumes per kernel variant in it (padded range,
+ * path count, plane type, sub-pixel) one sum + winner-take-all launch per
+ * variant instead.  Items with SGM_LR_FULL add their right-base costs,
+ * directions and rows to the same launches.
  * The aggregation is a persistent kernel whose wavefronts take (pair,
  * direction, slice group) work items, longest first, from a queue.  The
  * runner keeps a device workspace that grows to the largest batch seen;
@@ -218,7 +219,7 @@ int sgm_batch_compute(sgm_batch *b, const sgm_item *items, int n, sgm_stream_t s
 /* Kernel shape of the batched aggregation (results never depend on it):
  * lanes per horizontal slice (16 or 32) and per other slice (16 or 32) for
  * every pair; 0 keeps the default (16; 32 horizontal lanes for ranges above
- * 64 in a batch too small to fill the device). */
+ * 64 where the batch's slices then still fit the device at once). */
 int sgm_batch_set_tuning(sgm_batch *b, int lanes_h, int lanes_v);
 
 /* Workgroups (4 wavefronts each) of the persistent aggregation grid: 0, the

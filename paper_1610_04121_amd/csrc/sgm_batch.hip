@@ -54,34 +54,61 @@ __global__ __launch_bounds__(256) void census_batch_kernel(const BatchItem* item
 
 // Units 0 .. nx * H - 1 of a pair make its cost volume; with the full
 // left-right check, the next nx * H make the right-base costs.
-template <bool RB, int AUX>
+template <bool RB, int AUX, int RUN>
 __device__ inline void cost_batch_unit(const BatchItem& it, int ux, int y, int lane, uint64_t* smem) {
     const CostArgs a = RB ? CostArgs{it.census_r, it.census_l, it.cost_r, it.W, it.H, it.D, it.Dp, it.cmax}
                           : CostArgs{it.census_l, it.census_r, it.cost, it.W, it.H, it.D, it.Dp, it.cmax};
     if (it.Dp == 64)
-        cost_unit<RB, 64, 8, AUX>(a, ux, y, lane, smem);
+        cost_unit<RB, 64, RUN, AUX>(a, ux, y, lane, smem);
     else if (it.Dp == 128)
-        cost_unit<RB, 128, 8, AUX>(a, ux, y, lane, smem);
+        cost_unit<RB, 128, RUN, AUX>(a, ux, y, lane, smem);
     else
-        cost_unit<RB, 256, 8, AUX>(a, ux, y, lane, smem);
+        cost_unit<RB, 256, RUN, AUX>(a, ux, y, lane, smem);
 }
 
-template <int AUX>
+template <int AUX, int RUN>
 __global__ __launch_bounds__(kCostThreads) void cost_batch_kernel(const BatchItem* items, int n, int per_wave) {
     constexpr int kWaves = kCostThreads / 64;
-    __shared__ uint64_t words[kWaves][CostUnit<256, 8>::words];
+    __shared__ uint64_t words[kWaves][CostUnit<256, RUN>::words];  // the largest range needs the most
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int b = blockIdx.x;
     const BatchItem& it = items[find_item<&BatchItem::cost_blk0>(items, n, b)];
-    const int px = cost_unit_px(it.Dp, 8), nx = (it.W + px - 1) / px, per_map = nx * it.H;
+    const int px = cost_unit_px(it.Dp, RUN), nx = (it.W + px - 1) / px, per_map = nx * it.H;
     const int first = (b - it.cost_blk0) * kWaves * per_wave + wave;
     const int end = min(it.cost_r ? 2 * per_map : per_map, first + kWaves * per_wave);
     for (int unit = first; unit < end; unit += kWaves) {
         if (unit < per_map)
-            cost_batch_unit<false, AUX>(it, unit % nx, unit / nx, lane, words[wave]);
+            cost_batch_unit<false, AUX, RUN>(it, unit % nx, unit / nx, lane, words[wave]);
         else
-            cost_batch_unit<true, AUX>(it, (unit - per_map) % nx, (unit - per_map) / nx, lane, words[wave]);
+            cost_batch_unit<true, AUX, RUN>(it, (unit - per_map) % nx, (unit - per_map) / nx, lane, words[wave]);
     }
+}
+
+// The winner-take-all of small batches, all pairs in one launch.  Blocks 0 ..
+// H - 1 of a pair are its rows; with the full left-right check blocks H ..
+// 2H - 1 are the rows of the right-base SGM, whose winners are D_R.
+template <bool NT>
+__global__ __launch_bounds__(1024) void wta_batch_kernel(const BatchItem* items, int n) {
+    extern __shared__ uint32_t wta_smem[];
+    const int b = blockIdx.x;
+    const BatchItem& it = items[find_item<&BatchItem::wta_blk0>(items, n, b)];
+    const bool post = it.median || it.lrcheck;
+    const size_t plane = (size_t)it.W * it.H * it.Dp;
+    int y = b - it.wta_blk0;
+    WtaArgs a{it.lbuf, plane, post ? it.dl : it.out, (it.lrcheck && !it.lr_full) ? it.dr : nullptr,
+              it.W, it.H, it.D, it.Dp, it.P, it.subpixel, it.cost};
+    if (y >= it.H) {  // right-base rows: planes P .. 2P - 1, winners into D_R
+        y -= it.H;
+        a.lbuf = static_cast<const uint8_t*>(it.lbuf) + plane * it.P * (it.l16 ? 2 : 1);
+        a.cost = it.cost_r;
+        a.dl = it.dr;
+        a.dr = nullptr;
+        a.subpixel = 0;
+    }
+    if (it.l16)
+        wta_row<uint16_t, NT>(a, y, wta_smem);
+    else
+        wta_row<uint8_t, NT>(a, y, wta_smem);
 }
 
 __global__ __launch_bounds__(256) void post_batch_kernel(const BatchItem* items, int n) {
@@ -92,9 +119,9 @@ __global__ __launch_bounds__(256) void post_batch_kernel(const BatchItem* items,
     post_row(a, b - it.post_blk0, post_smem);
 }
 
-// Units of a pair's cost volumes.
-size_t cost_unit_count(const Plan& p) {
-    const size_t px = cost_unit_px(p.Dp, 8);
+// Units of a pair's cost volumes, `run` pixels a lane.
+size_t cost_unit_count(const Plan& p, int run) {
+    const size_t px = cost_unit_px(p.Dp, run);
     return (p.lr_full ? 2 : 1) * ((p.W + px - 1) / px) * p.H;
 }
 
@@ -241,9 +268,13 @@ struct BatchLaunch {
     std::vector<BatchItem> desc;
     std::vector<WorkItem> work;
     size_t census_blocks = 0, cost_blocks = 0, post_blocks = 0;
-    int cost_per_wave = 1;   // units a wavefront of the cost launch takes
+    int cost_run = 8;        // pixels a lane of the cost launch takes
+    int cost_per_wave = 1;   // units a wavefront of it takes
     bool cost_nt = false;    // its stores non-temporal
     size_t post_smem = 0;
+    // Small batches: the winner-take-all over whole planes, in one launch of
+    // wta_blocks (0: the row kernel).
+    size_t wta_blocks = 0, wta_smem = 0;
     // The row kernel is one launch per variant (padded range, path count,
     // plane type): pairs of a variant follow each other in desc.
     struct Rows {
@@ -280,31 +311,62 @@ int batch_build(const BatchParams& bp, const Plan* plans, uint8_t* const* ws_bas
     for (int i = 0; i < n; ++i) order[i] = i;
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return variant(a) < variant(b); });
     B.rows.clear();
-    // Cost volumes: 8-pixel units as in the single-pair launch.  From 16
-    // wavefronts per SIMD on, a wavefront takes two units for one look at the
-    // table (64 pairs, 316000 units: 711 us, one unit 740, four 719).
-    size_t cost_units = 0, cost_bytes = 0;
+    // Cost volumes: 8 pixels a lane, or 2 where 8 leave at most one wavefront
+    // per SIMD, as in the single-pair launch.  From 16 wavefronts per SIMD on,
+    // a wavefront takes two units for one look at the table (64 pairs, 316000
+    // units: 711 us, one unit 740, four 719).
+    size_t cost_units = 0, cost_bytes = 0, plane_bytes = 0, variants = 0;
     for (int i = 0; i < n; ++i) {
-        cost_units += cost_unit_count(plans[i]);
-        cost_bytes += (size_t)(plans[i].lr_full ? 2 : 1) * plans[i].W * plans[i].H * plans[i].Dp;
+        const Plan& p = plans[order[i]];
+        const size_t cells = (size_t)(p.lr_full ? 2 : 1) * p.W * p.H * p.Dp;
+        cost_units += cost_unit_count(p, 8);
+        cost_bytes += cells;
+        plane_bytes += cells * p.n_paths * (p.l16 ? 2 : 1);
+        variants += i == 0 || variant(order[i]) != variant(order[i - 1]);
     }
+    // the planes and cost volumes of the whole batch against the memory-side
+    // cache: the store policy of the single-pair path (Plan::nt_store)
+    B.nt = plane_bytes + cost_bytes > (size_t)kMallBytes;
+    // Whole planes and one winner-take-all launch, or checkpoints and a row
+    // launch per variant: a row launch takes 6 to 10 us however few rows it
+    // has, so the row kernel pays where a launch covers as much as a frame that
+    // takes it (bytes of planes here: 16-bit planes cost the winner-take-all
+    // twice as much).  Winner-take-all against row kernel (us): one 96x64 pair,
+    // D = 128, 8 paths 42.9, 47.1; three 160x120 pairs of different kinds 72.6,
+    // 88; nine 96x64 pairs, every range and path count 85, 145 (18 with
+    // sub-pixel ones 114, 248); eighteen 320x240 pairs, 53 MB a launch 624, 663;
+    // but nine with 16-bit planes, 107 MB 629, 490.
+    const bool wta = plane_bytes <= variants * (size_t)kRowKernelCells;
+    B.cost_run = cost_units <= 1024 ? 2 : 8;
     B.cost_per_wave = cost_units >= 16384 ? 2 : 1;
     B.cost_nt = cost_bytes > (size_t)kMallBytes;  // the policy of launch_cost
-    long long waves16 = 0;  // wavefronts of the aggregation at 16 lanes a slice
+    // wavefronts of the aggregation with 16 lanes a slice, and with 32
+    // horizontal ones for ranges above 64
+    long long waves16 = 0, waves32 = 0;
     for (int i = 0; i < n; ++i)
-        for (int r = 0; r < plans[i].n_paths; ++r)
-            waves16 += (plans[i].lr_full ? 2 : 1) * ((slice_count(plans[i].W, plans[i].H, direction(plans[i].n_paths, r)) + 3) / 4);
+        for (int r = 0; r < plans[i].n_paths; ++r) {
+            const Dir d = direction(plans[i].n_paths, r);
+            const int nsl = slice_count(plans[i].W, plans[i].H, d), nsgm = plans[i].lr_full ? 2 : 1;
+            waves16 += nsgm * ((nsl + 3) / 4);
+            waves32 += nsgm * (d.ry == 0 && plans[i].Dp > 64 ? (nsl + 1) / 2 : (nsl + 3) / 4);
+        }
+    const bool one = waves32 <= 1024, two = waves16 > 1024 && waves32 <= 2048;
     for (int i = 0; i < n; ++i) {
         const int src = order[i];
         const Plan& p = plans[src];
         const Workspace ws = workspace_carve(p, ws_base[src]);
         // the batch kernel has 32- and 16-lane groups; the runner's tuning,
         // when set, applies to every pair.  By default 16 lanes, which take
-        // the fewest instructions per cell, unless the whole batch is too
-        // small to give each SIMD a wavefront and its steps' length counts
-        // (64 mixed pairs: 16/16 7229 us, 32/16 7438; 8 small pairs, D <= 64:
-        // 109 and 114).
-        const int gh = bp.lanes_h ? bp.lanes_h : (p.Dp > 64 && waves16 <= 1024 ? 32 : 16);
+        // the fewest instructions per cell, but for ranges above 64 32
+        // horizontal ones, whose steps are shorter, where they fit one
+        // wavefront per SIMD (and rows are the longest slices), or two (what
+        // the persistent grid holds) if 16 do not fit one.  With 32 and with 16
+        // (us, D = 128, 4 paths): one 480x640 pair (560 wavefronts of 16 lanes,
+        // 800 with 32) 152, 138; two 451x377 (832, 1208) 161, 138; one 1280x720
+        // (1000, 1360) 305, 286; two 640x480 (1120, 1600) 218, 235; two 1242x375
+        // (1620, 1996) 292, 307; three 640x480 (1680, 2400) 293, 283; 64 mixed
+        // pairs 7438, 7229.
+        const int gh = bp.lanes_h ? bp.lanes_h : (p.Dp > 64 && ((one && p.W > p.H) || two) ? 32 : 16);
         const int gv = bp.lanes_v ? bp.lanes_v : 16;
         BatchItem& d = desc[i];
         d.left = items[src].left;
@@ -340,15 +402,21 @@ int batch_build(const BatchParams& bp, const Plan* plans, uint8_t* const* ws_bas
                                  : (size_t)2 * ((p.W + kCenTX - 1) / kCenTX) * ((p.H + kCenTY - 1) / kCenTY);
         d.cost_blk0 = (int)cost_blocks;
         const size_t cost_per = (size_t)(kCostThreads / 64) * B.cost_per_wave;
-        cost_blocks += (cost_unit_count(p) + cost_per - 1) / cost_per;
-        if (i == 0 || variant(src) != variant(order[i - 1]))
-            B.rows.push_back({p.Dp, i, 0, RowVariant{p.n_paths, p.l16, false, 2 * p.pmax <= 255, p.subpixel}, 0, 0, 1});
-        BatchLaunch::Rows& rw = B.rows.back();
-        rw.n += 1;
-        d.wta_blk0 = (int)rw.blocks;
-        rw.blocks += (size_t)nsgm * p.H;
-        rw.smem = std::max(rw.smem, row_smem_bytes(p.W, p.lrcheck && !p.lr_full));
-        rw.waves = std::max(rw.waves, row_waves(p.W, p.Dp, p.l16));
+        cost_blocks += (cost_unit_count(p, B.cost_run) + cost_per - 1) / cost_per;
+        if (wta) {
+            d.wta_blk0 = (int)B.wta_blocks;
+            B.wta_blocks += (size_t)nsgm * p.H;
+            B.wta_smem = std::max(B.wta_smem, row_smem_bytes(p.W, p.lrcheck && !p.lr_full));
+        } else {
+            if (i == 0 || variant(src) != variant(order[i - 1]))
+                B.rows.push_back({p.Dp, i, 0, RowVariant{p.n_paths, p.l16, false, 2 * p.pmax <= 255, p.subpixel}, 0, 0, 1});
+            BatchLaunch::Rows& rw = B.rows.back();
+            rw.n += 1;
+            d.wta_blk0 = (int)rw.blocks;
+            rw.blocks += (size_t)nsgm * p.H;
+            rw.smem = std::max(rw.smem, row_smem_bytes(p.W, p.lrcheck && !p.lr_full));
+            rw.waves = std::max(rw.waves, row_waves(p.W, p.Dp, p.l16));
+        }
         d.post_blk0 = (int)post_blocks;
         if (p.median || p.lrcheck) post_blocks += p.H;
         if (p.lrcheck) post_smem = std::max(post_smem, 2 * (size_t)p.W);
@@ -420,12 +488,6 @@ int batch_build(const BatchParams& bp, const Plan* plans, uint8_t* const* ws_bas
 
     // persistent grid: at most two wavefronts per SIMD (256 CUs x 4 SIMDs)
     B.blocks = std::min((int)quads.size(), bp.max_workgroups > 0 ? std::min(bp.max_workgroups, 512) : 512);
-    // the planes and cost volumes of the whole batch against the memory-side
-    // cache: the store policy of the single-pair path (Plan::nt_store)
-    long long fbytes = 0;
-    for (const BatchItem& d : desc)
-        fbytes += (long long)d.W * d.H * d.Dp * (d.P * (d.l16 ? 2 : 1) + 1) * (d.lr_full ? 2 : 1);
-    B.nt = fbytes > kMallBytes;
     B.generic = generic;
     B.any_adapt = any_adapt;
     B.census_blocks = census_blocks;
@@ -440,10 +502,16 @@ hipError_t batch_launch(const BatchParams& bp, const BatchLaunch& B, const Batch
     const int n = (int)B.desc.size();
     hipLaunchKernelGGL(census_batch_kernel, dim3((unsigned)B.census_blocks), dim3(256), 0, s, d_items, n,
                        B.generic ? 1 : 0, (bp.cw - 1) / 2, (bp.ch - 1) / 2, counter);
-    hipLaunchKernelGGL(B.cost_nt ? cost_batch_kernel<kStoreNT> : cost_batch_kernel<kStoreSc1>, dim3((unsigned)B.cost_blocks), dim3(kCostThreads), 0, s, d_items, n, B.cost_per_wave);
+    auto cost = B.cost_run == 2 ? cost_batch_kernel<kStoreSc1, 2>
+                : B.cost_nt     ? cost_batch_kernel<kStoreNT, 8>
+                                : cost_batch_kernel<kStoreSc1, 8>;
+    hipLaunchKernelGGL(cost, dim3((unsigned)B.cost_blocks), dim3(kCostThreads), 0, s, d_items, n, B.cost_per_wave);
     const int nquads = (int)(B.work.size() / kQuad);
-    (B.any_adapt ? launch_batch_agg_adapt : launch_batch_agg)(B.nt, B.blocks, d_items, d_work, nquads, counter, bp.P1,
-                                                              bp.P2, s);
+    (B.any_adapt ? launch_batch_agg_adapt : launch_batch_agg)(B.nt, B.wta_blocks == 0, B.blocks, d_items, d_work, nquads,
+                                                              counter, bp.P1, bp.P2, s);
+    if (B.wta_blocks > 0)
+        hipLaunchKernelGGL(B.nt ? wta_batch_kernel<true> : wta_batch_kernel<false>, dim3((unsigned)B.wta_blocks),
+                           dim3(1024), B.wta_smem, s, d_items, n);
     for (const BatchLaunch::Rows& r : B.rows) {
         RowLaunch a{};
         a.items = d_items + r.first;

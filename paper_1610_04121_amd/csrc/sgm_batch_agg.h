@@ -23,7 +23,8 @@ struct BatchItem {
     uint16_t* dr;
     int W, H, D, Dp, P, cmax, l16, median, lrcheck, thr, csct, gh, gv, subpixel, lr_full, adaptive;
     int census_blk0, cost_blk0, wta_blk0, post_blk0;  // first block in each launch (wta_blk0: in
-                                                      // the row launch of its kernel variant)
+                                                      // the winner-take-all launch or the row
+                                                      // launch of its kernel variant)
 };
 
 // One aggregation work item: S = 64 / G slices of one direction of one pair;
@@ -55,9 +56,10 @@ __device__ inline int find_item(const BatchItem* items, int n, int b) {
     return lo;
 }
 
-void launch_batch_agg(bool nt, int blocks, const BatchItem* items, const WorkItem* work, int nquads,
+// ckpt: the row kernel follows; else the winner-take-all over whole planes.
+void launch_batch_agg(bool nt, bool ckpt, int blocks, const BatchItem* items, const WorkItem* work, int nquads,
                       unsigned* queue_counter, int P1, int P2, hipStream_t stream);
-void launch_batch_agg_adapt(bool nt, int blocks, const BatchItem* items, const WorkItem* work, int nquads,
+void launch_batch_agg_adapt(bool nt, bool ckpt, int blocks, const BatchItem* items, const WorkItem* work, int nquads,
                             unsigned* queue_counter, int P1, int P2, hipStream_t stream);
 
 }  // namespace sgm

@@ -3,9 +3,9 @@
 
 namespace sgm {
 
-void launch_batch_agg(bool nt, int blocks, const BatchItem* items, const WorkItem* work, int nquads,
+void launch_batch_agg(bool nt, bool ckpt, int blocks, const BatchItem* items, const WorkItem* work, int nquads,
                       unsigned* queue_counter, int P1, int P2, hipStream_t stream) {
-    launch_batch_agg_t<false>(nt, blocks, items, work, nquads, queue_counter, P1, P2, stream);
+    launch_batch_agg_t<false>(nt, ckpt, blocks, items, work, nquads, queue_counter, P1, P2, stream);
 }
 
 }  // namespace sgm

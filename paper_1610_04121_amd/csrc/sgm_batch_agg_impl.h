@@ -12,15 +12,17 @@ namespace {
 using namespace dev;
 
 // NT: non-temporal L_r stores (the batch's planes exceed the memory-side
-// cache); ADAPT: adaptive P2 (the block's penalty table is in s.p2lut).
-template <typename LT, int Dp, bool NT, bool ADAPT>
+// cache); ADAPT: adaptive P2 (the block's penalty table is in s.p2lut); CKPT:
+// horizontal directions store what the row kernel needs, else whole planes.
+template <typename LT, int Dp, bool NT, bool ADAPT, bool CKPT>
 __device__ __attribute__((always_inline)) inline void aggregate_item(const SliceArgs& s, int kind, int g, int first,
                                                                      int lane) {
     if (kind == kHoriz) {
+        using Sink = std::conditional_t<CKPT, CkptSink, PlaneSink>;
         if (g == 32)
-            aggregate_wave<32, Dp / 32, LT, kHoriz, false, ADAPT, NT, CkptSink>(s, first, lane);
+            aggregate_wave<32, Dp / 32, LT, kHoriz, false, ADAPT, NT, Sink>(s, first, lane);
         else
-            aggregate_wave<16, Dp / 16, LT, kHoriz, false, ADAPT, NT, CkptSink>(s, first, lane);
+            aggregate_wave<16, Dp / 16, LT, kHoriz, false, ADAPT, NT, Sink>(s, first, lane);
     } else if (kind == kVert) {
         if (g == 32)
             aggregate_wave<32, Dp / 32, LT, kVert, false, ADAPT, NT>(s, first, lane);
@@ -36,22 +38,22 @@ __device__ __attribute__((always_inline)) inline void aggregate_item(const Slice
 
 // g: the work item's lanes per slice (its pair's horizontal or other group
 // width, by the direction's kind)
-template <typename LT, bool NT, bool ADAPT>
+template <typename LT, bool NT, bool ADAPT, bool CKPT>
 __device__ __attribute__((always_inline)) inline void aggregate_item_dp(const SliceArgs& s, int Dp, int kind, int g,
                                                                         int first, int lane) {
     if (Dp == 64)
-        aggregate_item<LT, 64, NT, ADAPT>(s, kind, g, first, lane);
+        aggregate_item<LT, 64, NT, ADAPT, CKPT>(s, kind, g, first, lane);
     else if (Dp == 128)
-        aggregate_item<LT, 128, NT, ADAPT>(s, kind, g, first, lane);
+        aggregate_item<LT, 128, NT, ADAPT, CKPT>(s, kind, g, first, lane);
     else
-        aggregate_item<LT, 256, NT, ADAPT>(s, kind, g, first, lane);
+        aggregate_item<LT, 256, NT, ADAPT, CKPT>(s, kind, g, first, lane);
 }
 
 // ANY_ADAPT: some pair of the batch uses the adaptive P2 (a second
 // instantiation, so batches without one keep the smaller kernel).  A
 // workgroup takes one quad of work items at a time, wavefront k its item k;
 // the quad's items have the same length, so its wavefronts finish together.
-template <bool NT, bool ANY_ADAPT>
+template <bool NT, bool ANY_ADAPT, bool CKPT>
 __global__ __launch_bounds__(256) void aggregate_batch_kernel(const BatchItem* items, const WorkItem* work,
                                                               int nquads, unsigned* queue_counter, int P1, int P2) {
     __shared__ uint16_t p2lut[ANY_ADAPT ? 256 : 1];
@@ -95,16 +97,17 @@ __global__ __launch_bounds__(256) void aggregate_batch_kernel(const BatchItem* i
             }
         }
         if (it.l16)
-            aggregate_item_dp<uint16_t, NT, ANY_ADAPT>(s, it.Dp, kind, g, w.first, lane);
+            aggregate_item_dp<uint16_t, NT, ANY_ADAPT, CKPT>(s, it.Dp, kind, g, w.first, lane);
         else
-            aggregate_item_dp<uint8_t, NT, ANY_ADAPT>(s, it.Dp, kind, g, w.first, lane);
+            aggregate_item_dp<uint8_t, NT, ANY_ADAPT, CKPT>(s, it.Dp, kind, g, w.first, lane);
     }
 }
 
 template <bool ANY_ADAPT>
-void launch_batch_agg_t(bool nt, int blocks, const BatchItem* items, const WorkItem* work, int nquads,
+void launch_batch_agg_t(bool nt, bool ckpt, int blocks, const BatchItem* items, const WorkItem* work, int nquads,
                         unsigned* queue_counter, int P1, int P2, hipStream_t stream) {
-    auto k = nt ? aggregate_batch_kernel<true, ANY_ADAPT> : aggregate_batch_kernel<false, ANY_ADAPT>;
+    auto k = ckpt ? (nt ? aggregate_batch_kernel<true, ANY_ADAPT, true> : aggregate_batch_kernel<false, ANY_ADAPT, true>)
+                  : (nt ? aggregate_batch_kernel<true, ANY_ADAPT, false> : aggregate_batch_kernel<false, ANY_ADAPT, false>);
     hipLaunchKernelGGL(k, dim3((unsigned)blocks), dim3(256), 0, stream, items, work, nquads, queue_counter, P1, P2);
 }
 
