@@ -41,7 +41,7 @@ __global__ __launch_bounds__(512) void row_kernel(RowLaunch k) {
 
 template <int Dp, int NV, bool SUB>
 hipError_t launch_row_t(const RowLaunch& a, const RowVariant& v, int blocks, int waves, size_t smem, hipStream_t stream) {
-    auto k = row_kernel<Dp, NV, uint16_t, true, false, SUB>;
+    auto k = v.nt ? row_kernel<Dp, NV, uint16_t, true, false, SUB> : row_kernel<Dp, NV, uint16_t, false, false, SUB>;
     if (!v.l16) {
         if (v.pair)
             k = v.nt ? row_kernel<Dp, NV, uint8_t, true, true, SUB> : row_kernel<Dp, NV, uint8_t, false, true, SUB>;

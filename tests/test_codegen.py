@@ -101,3 +101,30 @@ def test_f16_order_equals_unsigned_order_below_0x1000():
     # and 0x0FFF (the kernels' stand-in for a missing neighbour) is above every
     # real candidate: Cmax + largest penalty <= 255 < 0x0FFF
     assert float(np.uint16(0x0FFF).view(np.float16)) > float(np.uint16(255 + 255).view(np.float16))
+
+
+def _kernels(asm, pattern):
+    names = [n for n in _kernel_bodies(asm) if re.search(pattern, n) and f".amdhsa_kernel {n}\n" in asm]
+    assert names, pattern
+    return names
+
+
+@pytest.mark.parametrize("pattern", [r"10row_kernel", r"11cost_kernel", r"17cost_batch_kernel", r"10wta_kernel",
+                                     r"16wta_batch_kernel"])
+def test_row_cost_and_wta_kernels_do_not_spill(device_asm, pattern):
+    for n in _kernels(device_asm, pattern):
+        m = re.search(r"; ScratchSize: (\d+)", device_asm[device_asm.index(n + ":"):])
+        assert m and int(m.group(1)) == 0, n
+
+
+def test_row_kernels_load_planes_by_the_policy_they_were_stored_with(device_asm):
+    # row_kernel<Dp, NV, plane type, NT, PAIR, SUB>: both load policies of
+    # every range, path set and plane type, and no non-temporal load where the
+    # planes were stored to stay in the memory-side cache
+    bodies = _kernel_bodies(device_asm)
+    seen = set()
+    for n in _kernels(device_asm, r"10row_kernel"):
+        dp, nv, lt, nt = re.search(r"10row_kernelILi(\d+)ELi(\d+)E([ht])Lb([01])E", n).groups()
+        seen.add((dp, nv, lt, nt))
+        assert bool(re.search(r"buffer_load\S+ [^\n]*\bnt\b", bodies[n])) == (nt == "1"), n
+    assert len(seen) == 3 * 3 * 2 * 2
