@@ -132,7 +132,7 @@ int sgm_compute(sgm_ctx *ctx, const uint8_t *left, const uint8_t *right, uint16_
  *   launch.  Bit SGM_TUNE_FINAL_PASS: the last path direction (right-to-left;
  *   left-to-right with 2 paths) runs fused with the sum over directions and
  *   the winner-take-all (Sec. 3.3), so its L_r is never stored; used where
- *   the planes are u8, the cost volume is stored and neither SGM_LR_FULL
+ *   Cmax + P2 <= 255, the cost volume is stored and neither SGM_LR_FULL
  *   nor SGM_ADAPTIVE_P2 is set, otherwise ignored.  Bit
  *   SGM_TUNE_POST_IN_WTA: the median (Sec. 2) and left-right check (Sec. 5) run
  *   inside the winner-take-all launch (the block that completes the raw rows

@@ -392,8 +392,11 @@ hipError_t launch_aggregate(const Plan& p, const Workspace& ws, hipStream_t stre
     return launch_agg_256(a, v, stream);
 }
 
+// Not past Cmax + pmax = 255: byte planes of L - C hold more, but the plain
+// route, which such frames always took, is faster (640x480, 4 paths, P2 = 250:
+// D = 64 64 us against 111, D = 128 95 against 139).
 bool final_pass_active(const Plan& p) {
-    if (!p.final_pass || p.l16 || p.lr_full || p.adaptive || fused_aggregation(p)) return false;
+    if (!p.final_pass || p.wide || p.lr_full || p.adaptive || fused_aggregation(p)) return false;
     return final_smem_bytes(p.Dp, p.W, p.lrcheck) <= 64 * 1024;
 }
 

@@ -113,8 +113,8 @@ bool row_kernel_active(const Plan& p, bool post_in_wta);
 hipError_t launch_row(const Plan& p, const Workspace& ws, const uint8_t* left, const uint8_t* right, uint16_t* out,
                       hipStream_t stream);
 // Whether the final pass replaces the last direction's aggregation and the
-// WTA launch: the tuning asks for it and the plan allows it (u8 planes, the
-// cost volume, no full check, no adaptive P2, its LDS fits).
+// WTA launch: the tuning asks for it and the plan allows it (Cmax + pmax <=
+// 255, the cost volume, no full check, no adaptive P2, its LDS fits).
 bool final_pass_active(const Plan& p);
 // The final pass: after launch_aggregate(..., skip_last = true); writes the
 // raw maps (or `out` when no post stage follows); s_out (debug): S u16
