@@ -1819,11 +1819,15 @@ __host__ __device__ inline size_t final_smem_bytes(int Dp, int W, bool right) {
     return (size_t)2 * 16 * R * Dp + (right ? (size_t)4 * R * (W + kWtaGuard) : 0);
 }
 
-// Chunks of plane loads a consumer lane keeps in flight, within about 64
-// registers: 4 * M * NPL registers per chunk.
-template <int M, int NPL>
+// Chunks of plane loads (NPL: the stored planes and the cost volume) a consumer
+// lane keeps in flight, within about 64 registers: 4 * M * NPL registers per
+// chunk.  Two chunks of 4 loads of 2 items fill them (4 paths: 640x480, D = 128
+// 139 us, one chunk 153; 1280x720, D = 64 247, 291) but with 128 levels and
+// non-temporal planes they cost more than they hide (1280x720 446, 387), and
+// with 256 levels and 2 paths they spill.
+template <int Dp, int M, int NPL, bool NT>
 struct FinalAhead {
-    static constexpr int n = 14 / (M * NPL);
+    static constexpr int n = (Dp == 64 || (Dp == 128 && !NT) ? 16 : 14) / (M * NPL);
     static constexpr int N = n < 1 ? 1 : (n > 3 ? 3 : n);
 };
 
@@ -1944,7 +1948,7 @@ __device__ inline void final_pass_block(const FinalArgs& f, int blk, uint8_t* sm
 #pragma unroll
         for (int p = 0; p < NPL; ++p) rp[p] = buffer_rsrc(f.planes + f.plane * p, (uint32_t)f.plane);
         rp[NPL] = buffer_rsrc(f.agg.cost, (uint32_t)f.plane);
-        constexpr int A = FinalAhead<L::M, NPL + 1>::N;
+        constexpr int A = FinalAhead<Dp, L::M, NPL + 1, NT>::N;
         // plane bytes of the lane's M items of chunks c .. c + A - 1, slot c % A
         uint4 q[A][L::M][NPL + 1];
         auto item = [&](int c, int m) { return FinalItem<Dp>(f, y0, c, ctid + m * 64 * L::NC); };
