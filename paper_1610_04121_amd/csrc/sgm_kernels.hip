@@ -308,7 +308,10 @@ static void fill_agg_args(const Plan& p, const Workspace& ws, const uint8_t* lef
 // 64/32 (800) 112, 32/16 135; 640x480, D = 128, 8 paths: 64/16 (1920, 0.94 of
 // two rounds) 155, 32/16 (1440, 0.70) 161; 800x600, D = 128, 8 paths: 32/32
 // (3000, 0.98) 255, 32/16 (1800, 0.88) 272; 1242x375, D = 128, 8 paths: 64/16
-// (2613, 0.85) 248, 32/16 (2238, 0.73) 262.  With 64 levels a 16-lane step is
+// (2613, 0.85) 248, 32/16 (2238, 0.73) 262; D = 256: 1000x600, 4 paths 16/16
+// (800) 300, 32/16 (1100) 330, 32/32 (1600) 307; 1080x720 346, 374, 356; 600x800
+// 251, 284, 256; 1242x375, 4 paths 32/16 (998) 253, 16/16 267; 1242x375, 8 paths
+// 64/16 446, 32/16 470, 16/16 516.  With 64 levels a 16-lane step is
 // as short as a 32-lane one (320x240: 43.2 and 45.0), except with many
 // directions over several rounds (1242x375, 8 paths: 32/16 151, 16/16 159).
 // 64 horizontal lanes beyond one round only pay with diagonals (640x480 4
@@ -326,6 +329,10 @@ void default_lanes(const Plan& p, int* gh, int* gv) {
         *gh = h;
         *gv = v;
     };
+    // a step that computes its costs loads a census word per level of a lane:
+    // the fewest levels (256 levels, 4 paths: 640x480 256 us, 32/16 508; 1000x600
+    // 563, 16/16 1084, 32/16 983; 16-bit planes 808, 1726 and 1450)
+    if (p.Dp == 256 && fused_aggregation(p)) return set(64, 32);
     if (p.Dp == 64) {
         const bool many = waves(16, 16) > kSimds && nsgm * p.n_paths >= 8;
         return many ? set(32, 16) : set(16, 16);
@@ -369,7 +376,10 @@ static int slice_segments(const Plan& p, int gh, int gv, bool checkpoints) {
     return ratio > 2.3 && p.n_paths == 4 ? 4 : 2;
 }
 
-// (it stores L_r itself, which byte planes hold up to Cmax + pmax = 255)
+// It stores L_r itself, which byte planes hold up to Cmax + pmax = 255; past
+// that, up to pmax = 255, the stored-cost aggregation on byte planes of L - C
+// takes its place, which is 2 to 7 times as fast as this one on 16-bit planes
+// (P2 = 220: 640x480, D = 128, 4 paths 96 us and 222; 320x240, D = 256 60 and 275).
 bool fused_aggregation(const Plan& p) { return p.fused && !p.lr_full && !p.adaptive && (p.l16 || !p.wide); }
 
 hipError_t launch_aggregate(const Plan& p, const Workspace& ws, hipStream_t stream, const uint8_t* left,

@@ -58,3 +58,16 @@ def test_final_pass_runs_where_a_byte_holds_the_summed_path_cost(routes):
         assert at["final"] == 1
         assert past["final"] == p2_255["final"] == p2_256["final"] == 0
         assert [r["l16"] for r in (at, past, p2_255, p2_256)] == [0, 0, 0, 1]
+
+
+def test_census_computing_aggregation_takes_the_fewest_levels_per_lane(routes):
+    for W, H, P2, P in ((640, 480, 86, 4), (1000, 600, 86, 4), (1000, 600, 300, 8), (320, 240, 300, 2)):
+        (r,) = routes((W, H, 256, 7, P2, P, FUSED))
+        assert (r["fused"], r["gh"], r["gv"]) == (1, 64, 32)
+
+
+def test_workspace_does_not_depend_on_the_plane_type_chosen(routes):
+    # past Cmax + P2 = 255 the planes had 16 bits each
+    a, b, c = routes(*[(640, 480, 128, 7, P2, 4, 0) for P2 in (193, 194, 256)])
+    assert b["bytes"] == c["bytes"] > a["bytes"]
+    assert (a["l16"], b["l16"], c["l16"]) == (0, 0, 1)
