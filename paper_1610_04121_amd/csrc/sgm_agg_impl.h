@@ -96,7 +96,7 @@ __global__ __launch_bounds__(256) void aggregate_kernel(AggArgs a) {
             walk(integral_constant<int, 32>{}, kind);
         else
             walk(integral_constant<int, 16>{}, kind);
-    } else {
+    } else if constexpr (!SPLIT) {  // (only path sets without diagonals are split)
         const integral_constant<int, kDiag> kind;
         if (a.gv == 32)
             walk(integral_constant<int, 32>{}, kind);

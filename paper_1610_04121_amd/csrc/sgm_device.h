@@ -985,7 +985,8 @@ struct Split {
 };
 
 // ADAPT: the P2 of each step adapts to the base image's intensity change
-// along the path (adaptive_p2); the intensities are prefetched with the costs.
+// along the path (adaptive_p2): a block's intensities are loaded a block ahead,
+// one step per lane, and looked up once per block.
 template <int G, int CPL, typename LT, int KIND, bool FUSED, bool ADAPT = false, bool NT = false,
           typename SINK = PlaneSink, bool SPLIT = false>
 __device__ inline void aggregate_wave(const SliceArgs& a, int first_slice, int lane, SINK* sink = nullptr,
@@ -993,7 +994,8 @@ __device__ inline void aggregate_wave(const SliceArgs& a, int first_slice, int l
     constexpr bool kCkpt = std::is_same_v<SINK, CkptSink>;
     constexpr bool kToPlane = std::is_same_v<SINK, PlaneSink> || kCkpt;
     static_assert(!kCkpt || (KIND == kHoriz && !FUSED), "checkpoints are for horizontal directions");
-    static_assert(!SPLIT || (kToPlane && !FUSED && sizeof(LT) == 1), "segments are for byte planes of L - C");
+    static_assert(!SPLIT || (kToPlane && !FUSED && sizeof(LT) == 1 && KIND != kDiag),
+                  "segments are for byte planes of L - C of axis-aligned directions");
     static_assert(!(FUSED && ADAPT), "adaptive P2 uses the cost-volume variant");
     constexpr int NP = CPL / 2;
     constexpr int Dp = G * CPL;
@@ -1085,12 +1087,6 @@ __device__ inline void aggregate_wave(const SliceArgs& a, int first_slice, int l
     cur.t = t_begin;
     const int t_pos = max(t_begin, 0);
     cur.x = KIND == kHoriz ? (rx > 0 ? t_pos : W - 1 - t_pos) : first_slice;
-    if constexpr (KIND == kDiag) {
-        if (t_pos > 0) {  // a diagonal wraps once every W steps
-            cur.x = (first_slice + rx * t_pos) % W;
-            cur.x += cur.x < 0 ? W : 0;
-        }
-    }
     cur.pix = KIND == kHoriz ? first_slice * W + cur.x : (ry > 0 ? t_pos : H - 1 - t_pos) * W + cur.x;
     // a position stays on the slice's last step, so the lookahead never
     // leaves the slice
@@ -1423,20 +1419,9 @@ __device__ inline void aggregate_wave(const SliceArgs& a, int first_slice, int l
         typename Raw<CPL>::T e_old{};
         auto before = [&] {
             if constexpr (fixing) {
-                // position of the block's last step
-                Pos p = cur;
-                if constexpr (KIND == kDiag) {
-                    const int row0 = p.pix - p.x + (PF - 1) * ry * W;
-                    p.x += (PF - 1) * rx;
-                    while (p.x < 0) p.x += W;
-                    while (p.x >= W) p.x -= W;
-                    p.pix = row0 + p.x;
-                } else {
-                    p.pix += (PF - 1) * pstep;
-                }
-                // device scope: past this CU's cache, which may hold the line
-                // from before another wavefront stored it
-                const uint32_t ofs = (uint32_t)((p.pix + lane_px(p)) * Dp + qofs);
+                // the block's last step; device scope: past this CU's cache,
+                // which may hold the line from before another wavefront stored it
+                const uint32_t ofs = (uint32_t)((cur.pix + (PF - 1) * pstep + jl0) * Dp + qofs);
                 if constexpr (CPL == 2) {
                     e_old = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rl, ofs, 0, 16);
                 } else if constexpr (CPL == 4) {

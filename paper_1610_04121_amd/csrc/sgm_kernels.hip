@@ -139,7 +139,9 @@ bool plan_finish(Plan& p, const char** why) {
     // Normal stores leave a frame's planes in the 256 MiB memory-side cache
     // for the row kernel (or WTA) to read back.  When the planes and the cost volume
     // do not fit, the dirty planes would be written back while the WTA reads,
-    // so they are stored non-temporally instead.
+    // so they are stored non-temporally instead.  (The count is of whole planes
+    // in every direction, also for frames that keep checkpoints of the
+    // horizontal ones and move less.)
     {
         const long long cells = (long long)p.W * p.H * p.Dp;
         const long long nsgm = p.lr_full ? 2 : 1;
@@ -496,6 +498,11 @@ hipError_t launch_row(const Plan& p, const Workspace& ws, const uint8_t* left, c
 }
 
 hipError_t launch_wta(const Plan& p, const Workspace& ws, uint16_t* out, hipStream_t stream, bool post_in_wta) {
+    // Without the post stage inside, frames come here up to kRowKernelCells
+    // cell-paths, whose planes and costs (at most 3/2 a byte plane's cells, 5/2
+    // a 16-bit one's, with 2 paths) are stored non-temporally only for two SGMs
+    // on 16-bit planes, or with the census-computing aggregation, whose never are.
+    static_assert(2 * 3 * kRowKernelCells / 2 <= kMallBytes && 5 * kRowKernelCells / 2 <= kMallBytes, "unreached variants");
     const bool nt = planes_nt(p);
     const bool post = p.median || p.lrcheck;
     const bool fold = post_in_wta && post;
@@ -518,7 +525,7 @@ hipError_t launch_wta(const Plan& p, const Workspace& ws, uint16_t* out, hipStre
         auto k = fold ? (p.l16 ? (nt ? wta_pair_kernel<uint16_t, true, true> : wta_pair_kernel<uint16_t, false, true>)
                                : (nt ? wta_pair_kernel<uint8_t, true, true> : wta_pair_kernel<uint8_t, false, true>))
                       : (p.l16 ? (nt ? wta_pair_kernel<uint16_t, true, false> : wta_pair_kernel<uint16_t, false, false>)
-                               : (nt ? wta_pair_kernel<uint8_t, true, false> : wta_pair_kernel<uint8_t, false, false>));
+                               : wta_pair_kernel<uint8_t, false, false>);
         hipLaunchKernelGGL(k, dim3(2 * p.H), dim3(1024), smem, stream, l, r);
         return hipGetLastError();
     }
@@ -534,8 +541,7 @@ hipError_t launch_wta(const Plan& p, const Workspace& ws, uint16_t* out, hipStre
     // exceed the memory-side cache and the aggregation stored them so
     auto k = fold ? (p.l16 ? (nt ? wta_kernel<uint16_t, true, true> : wta_kernel<uint16_t, false, true>)
                            : (nt ? wta_kernel<uint8_t, true, true> : wta_kernel<uint8_t, false, true>))
-                  : (p.l16 ? (nt ? wta_kernel<uint16_t, true, false> : wta_kernel<uint16_t, false, false>)
-                           : (nt ? wta_kernel<uint8_t, true, false> : wta_kernel<uint8_t, false, false>));
+                  : (p.l16 ? wta_kernel<uint16_t, false, false> : wta_kernel<uint8_t, false, false>);
     hipLaunchKernelGGL(k, dim3(p.H), dim3(1024), smem, stream, a);
     return hipGetLastError();
 }

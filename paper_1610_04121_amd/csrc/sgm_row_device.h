@@ -35,7 +35,9 @@ struct RowArgs {
     int subpixel;  // sub-pixel output of this SGM (its kernel is the SUB variant)
 };
 
-// Bytes of LDS a row takes.
+// Bytes of LDS of a row's right-view keys; its table of P2 by intensity change
+// (256 u16) lies beside them.
+static_assert(4 * (kMaxWidth + kWtaGuard) + 512 <= 64 * 1024, "a row's LDS at the largest width");
 __host__ __device__ inline size_t row_smem_bytes(int W, bool right) { return right ? 4 * (size_t)(W + kWtaGuard) : 0; }
 
 // One step of Eq. 3 for groups of G lanes: E = min(R - m, P2), L = C + E,
