@@ -40,7 +40,8 @@ WORKLOAD = "vga_640x480_d128_p4"
 METRIC = "frames/s and Gcells/s (W·H·D·paths) at 640x480 D=128; p50/p99 latency served"
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "aggregate_vga_640x480_d128_p4_traffic.json")
 KERNEL_SRCS = [os.path.join(ROOT, "paper_1610_04121_amd", "csrc", f)
-               for f in ("sgm_device.h", "sgm_kernels.hip", "sgm_agg.h", "sgm_agg_impl.h", "sgm_common.h")]
+               for f in ("sgm_device.h", "sgm_kernels.hip", "sgm_agg.h", "sgm_agg_impl.h", "sgm_common.h",
+                         "sgm_row.h", "sgm_row_device.h", "sgm_row_impl.h")]
 
 
 def _kernel_sha() -> str:
