@@ -204,8 +204,8 @@ typedef struct sgm_batch sgm_batch;
 sgm_batch *sgm_batch_create(int P1, int P2, int census_w, int census_h);
 
 /* Enqueues all n items on `stream`: one census, one cost, one aggregation, one
- * sum + winner-take-all and one median + LR launch for the whole batch; with
- * more than 72 MiB of direction volumes per kernel variant in it (padded range,
+ * sum + winner-take-all and one median + LR launch for the whole batch; above
+ * a size that grows with the number of kernel variants in it (padded range,
  * path count, plane type, sub-pixel) one sum + winner-take-all launch per
  * variant instead.  Items with SGM_LR_FULL add their right-base costs,
  * directions and rows to the same launches.

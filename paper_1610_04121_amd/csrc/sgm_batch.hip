@@ -316,27 +316,33 @@ int batch_build(const BatchParams& bp, const Plan* plans, uint8_t* const* ws_bas
     // a wavefront takes two units for one look at the table (64 pairs, 316000
     // units: 711 us, one unit 740, four 719).
     size_t cost_units = 0, cost_bytes = 0, plane_bytes = 0, variants = 0;
+    bool wide_range = false;  // some range above 64
     for (int i = 0; i < n; ++i) {
         const Plan& p = plans[order[i]];
         const size_t cells = (size_t)(p.lr_full ? 2 : 1) * p.W * p.H * p.Dp;
         cost_units += cost_unit_count(p, 8);
         cost_bytes += cells;
         plane_bytes += cells * p.n_paths * (p.l16 ? 2 : 1);
+        wide_range = wide_range || p.Dp > 64;
         variants += i == 0 || variant(order[i]) != variant(order[i - 1]);
     }
     // the planes and cost volumes of the whole batch against the memory-side
     // cache: the store policy of the single-pair path (Plan::nt_store)
     B.nt = plane_bytes + cost_bytes > (size_t)kMallBytes;
     // Whole planes and one winner-take-all launch, or checkpoints and a row
-    // launch per variant: a row launch takes 6 to 10 us however few rows it
-    // has, so the row kernel pays where a launch covers as much as a frame that
-    // takes it (bytes of planes here: 16-bit planes cost the winner-take-all
-    // twice as much).  Winner-take-all against row kernel (us): one 96x64 pair,
-    // D = 128, 8 paths 42.9, 47.1; three 160x120 pairs of different kinds 72.6,
-    // 88; nine 96x64 pairs, every range and path count 85, 145 (18 with
-    // sub-pixel ones 114, 248); eighteen 320x240 pairs, 53 MB a launch 624, 663;
-    // but nine with 16-bit planes, 107 MB 629, 490.
-    const bool wta = plane_bytes <= variants * (size_t)kRowKernelCells;
+    // launch per variant.  The row kernel saves the horizontal planes' bytes;
+    // its launch takes longer however few rows it has (8 us and 4 with 128
+    // levels), and each further one 6 to 10 us.  The line is where the two meet,
+    // in bytes of planes.  Winner-take-all against row kernel (us), one variant:
+    // D = 64, 4 paths, one 160x120 pair (5 MB) 41.5, 42.1, two 240x180 (22 MB)
+    // 62.2, 61.3, a served burst of 16 small pairs 254, 242; D = 128, 4 paths,
+    // one 160x120 pair (10 MB) 45.5, 48.3, two 240x180 (44 MB) 83.3, 83.5; D =
+    // 256, one 240x180 pair (44 MB) 72.9, 74.9.  More variants: three 160x120
+    // pairs of different kinds 72.6, 88; nine 96x64 pairs of every range and path
+    // count 85, 145 (18 with sub-pixel ones 114, 248); eighteen 320x240 pairs
+    // (963 MB) 624, 663; but nine on 16-bit planes (963 MB) 629, 490.
+    const size_t line = ((variants - 1) * 72 + (wide_range ? 40 : 12)) << 20;
+    const bool wta = plane_bytes <= line;
     B.cost_run = cost_units <= 1024 ? 2 : 8;
     B.cost_per_wave = cost_units >= 16384 ? 2 : 1;
     B.cost_nt = cost_bytes > (size_t)kMallBytes;  // the policy of launch_cost

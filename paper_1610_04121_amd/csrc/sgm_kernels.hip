@@ -461,6 +461,15 @@ hipError_t launch_aggregate_wta(const Plan& p, const Workspace& ws, const uint8_
     return e;
 }
 
+// The row kernel trades two plane passes for running the horizontal
+// directions twice, so it pays where the planes' bytes set the time.  The
+// whole call with plain WTA against row kernel (us, one frame): 320x240 D = 64
+// 4 paths (19.7 M cell-paths) 44.6 / 44.4, 320x240 D = 128 8 paths (79 M) 59.8 /
+// 60.7, 451x377 D = 128 2 paths (44 M) 68.2 / 69.8, 640x480 D = 64 4 paths
+// (79 M) 79.3 / 76.7, 640x480 D = 128 4 paths (157 M) 99.8 / 94.8, 1280x720
+// D = 128 8 paths (944 M) 491 / 421; 96x64 D = 64 4 paths (1.6 M) 24.0 / 25.6.
+constexpr long long kRowKernelCells = 72ll << 20;
+
 bool row_kernel_active(const Plan& p, bool post_in_wta) {
     return (long long)p.W * p.H * p.Dp * p.n_paths > kRowKernelCells && !final_pass_active(p) && !fused_aggregation(p) &&
            !post_in_wta;

@@ -32,15 +32,6 @@ hipError_t launch_row_64(const RowLaunch& a, const RowVariant& v, int blocks, in
 hipError_t launch_row_128(const RowLaunch& a, const RowVariant& v, int blocks, int waves, size_t smem, hipStream_t stream);
 hipError_t launch_row_256(const RowLaunch& a, const RowVariant& v, int blocks, int waves, size_t smem, hipStream_t stream);
 
-// The row kernel trades two plane passes for running the horizontal
-// directions twice, so it pays where the planes' bytes set the time.  The
-// whole call with plain WTA against row kernel (us, one frame): 320x240 D = 64
-// 4 paths (19.7 M cell-paths) 44.6 / 44.4, 320x240 D = 128 8 paths (79 M) 59.8 /
-// 60.7, 451x377 D = 128 2 paths (44 M) 68.2 / 69.8, 640x480 D = 64 4 paths
-// (79 M) 79.3 / 76.7, 640x480 D = 128 4 paths (157 M) 99.8 / 94.8, 1280x720
-// D = 128 8 paths (944 M) 491 / 421; 96x64 D = 64 4 paths (1.6 M) 24.0 / 25.6.
-inline constexpr long long kRowKernelCells = 72ll << 20;
-
 // Wavefronts of a row's workgroup: a wavefront takes 4 segments at a time (2
 // with 256 levels).  8 wavefronts put two on each SIMD of a CU; 5 or 7 leave
 // SIMDs unequally loaded (1242x375, D = 128, 8 paths, whole call: 275, 265 and

@@ -1,7 +1,8 @@
 """The two ways a batch sums and takes winners: one winner-take-all launch over
-whole planes where a row launch (one per padded range, path count, plane type
-and sub-pixel option) would cover no more than 72 MiB of planes on average, and
-the row kernel above that.  Batches on both sides of the line, with every
+whole planes up to a number of plane bytes, and the row kernel, one launch per
+kernel variant (padded range, path count, plane type and sub-pixel option),
+above.  The line is 12 MiB for one variant with 64 levels, 40 MiB with more, and
+72 MiB more for each further variant.  Batches on both sides of it, with every
 option; the row kernel's widths beside a pair that is large enough for it; and
 the two pixel counts of the cost launch."""
 import numpy as np
@@ -12,7 +13,7 @@ from paper_1610_04121_amd import sgm as api
 
 pytestmark = pytest.mark.gpu
 
-LINE = 72 << 20
+LARGE = 72 << 20  # above the line of one variant
 WIDTHS = [1, 2, 7, 8, 9, 15, 16, 17, 31, 33, 63, 64, 65, 127, 130, 257, 530]
 
 
@@ -61,15 +62,19 @@ def test_small_mixed_batch(gpu, P1, P2):
     _run(gpu, shapes, P1, P2, P2)
 
 
-@pytest.mark.parametrize("W,H,D,P,P2,opts", [
-    (576, 512, 64, 4, 86, dict(lrcheck=True)), (577, 512, 64, 4, 86, dict(lrcheck=True)),  # the line, and past it
-    (288, 256, 100, 4, 86, dict(lr_full=True, lrcheck=True)), (289, 256, 100, 2, 300, dict(lr_full=True, lrcheck=True)),
+FULL = dict(lr_full=True, lrcheck=True)
+
+
+@pytest.mark.parametrize("shapes,P2,mib", [
+    ([(256, 192, 64, 4, dict(lrcheck=True))], 86, 12), ([(257, 192, 64, 4, dict(lrcheck=True))], 86, 12),  # at the line, past it
+    ([(256, 160, 100, 4, FULL)], 86, 40), ([(257, 160, 100, 2, FULL)], 300, 40),
+    ([(512, 256, 128, 4, {}), (512, 384, 50, 4, {})], 86, 112), ([(513, 256, 128, 4, {}), (512, 384, 50, 4, {})], 86, 112),
 ])
-def test_line_between_the_routes(gpu, W, H, D, P, P2, opts):
-    planes = W * H * _padded(D) * P * (2 if P2 > 255 else 1) * (2 if opts.get("lr_full") else 1)
-    assert abs(planes - LINE) < LINE // 256
-    print(f"line {W}x{H} D={D} P={P} P2={P2} {opts}: {planes - LINE:+d} bytes", flush=True)
-    _run(gpu, [(W, H, D, P, opts)], 7, P2, W)
+def test_line_between_the_routes(gpu, shapes, P2, mib):
+    planes = sum(W * H * _padded(D) * P * (2 if P2 > 255 else 1) * (2 if o.get("lr_full") else 1) for W, H, D, P, o in shapes)
+    assert 0 <= planes - (mib << 20) < 1 << 18
+    print(f"line {shapes} P2={P2}: {planes - (mib << 20):+d} bytes", flush=True)
+    _run(gpu, shapes, 7, P2, shapes[0][0])
 
 
 @pytest.mark.parametrize("opts", [{}, dict(lrcheck=True, median=True), dict(lrcheck=True, subpixel=True),
@@ -79,7 +84,7 @@ def test_line_between_the_routes(gpu, W, H, D, P, P2, opts):
 def test_row_kernel_widths_beside_a_large_pair(gpu, D, P, P1, P2, opts):
     print(f"row kernel D={D} P={P} P1={P1} P2={P2} {opts}", flush=True)
     W = 640
-    large = (W, LINE // (W * _padded(D) * P) + 1, D, P, opts)
+    large = (W, LARGE // (W * _padded(D) * P) + 1, D, P, opts)
     # (the large pair is there for the route; smaller tests cover its kind)
     _run(gpu, [(w, 3 + k % 4, D, P, opts) for k, w in enumerate(WIDTHS)] + [large], P1, P2, D + P, compare=len(WIDTHS))
 
@@ -95,7 +100,7 @@ def test_widest_pair_by_both_routes(gpu):
     """16000 columns with the right view: the keys of a row and the row
     kernel's penalty table together are 64 KiB of LDS."""
     for H, D in ((3, 128), (10, 256)):
-        assert (16000 * H * _padded(D) * 2 > LINE) == (H == 10)
+        assert (16000 * H * _padded(D) * 2 > LARGE) == (H == 10)
         print(f"widest pair 16000x{H} D={D}", flush=True)
         _run(gpu, [(16000, H, D, 2, dict(lrcheck=True, median=True))], 7, 86, H)
 
@@ -103,7 +108,7 @@ def test_widest_pair_by_both_routes(gpu):
 def test_widest_frame_in_the_row_kernel(gpu):
     import torch
     W, H, D = 16000, 10, 256
-    assert W * H * D * 2 > LINE
+    assert W * H * D * 2 > LARGE
     print(f"widest frame {W}x{H} D={D}", flush=True)
     l, r = _pair(np.random.default_rng(5), W, H)
     s = api.SGM(W, H, D, 7, 86, 2, lrcheck=True)
